@@ -76,6 +76,10 @@ fdmt_status_t upload(fdmt::Plan &p) {
   const size_t off_adj_order = reserve(p.adj.order.size() * sizeof(int32_t));
   const size_t off_sterms = reserve(p.fwd.sterms.size() * sizeof(fdmt::StagedTerm));
   const size_t off_sheads = reserve(p.fwd.sheads.size() * sizeof(int32_t));
+  const size_t off_biplaces = reserve(p.block_iplaces.size() * sizeof(fdmt::InTerm));
+  const size_t off_bplaces = reserve(p.block_places.size() * sizeof(fdmt::Term));
+  const size_t off_boffs = reserve(p.fwd.block_offs.size() * sizeof(int32_t));
+  const size_t off_bheads = reserve(p.fwd.block_heads.size() * sizeof(int32_t));
 
   std::vector<unsigned char> host(bytes, 0);
   for (int l = 1; l <= T.levels; ++l) {
@@ -107,6 +111,14 @@ fdmt_status_t upload(fdmt::Plan &p) {
     std::memcpy(host.data() + off_sterms, p.fwd.sterms.data(), p.fwd.sterms.size() * sizeof(fdmt::StagedTerm));
   if (!p.fwd.sheads.empty())
     std::memcpy(host.data() + off_sheads, p.fwd.sheads.data(), p.fwd.sheads.size() * sizeof(int32_t));
+  if (!p.block_iplaces.empty())
+    std::memcpy(host.data() + off_biplaces, p.block_iplaces.data(), p.block_iplaces.size() * sizeof(fdmt::InTerm));
+  if (!p.block_places.empty())
+    std::memcpy(host.data() + off_bplaces, p.block_places.data(), p.block_places.size() * sizeof(fdmt::Term));
+  if (!p.fwd.block_offs.empty())
+    std::memcpy(host.data() + off_boffs, p.fwd.block_offs.data(), p.fwd.block_offs.size() * sizeof(int32_t));
+  if (!p.fwd.block_heads.empty())
+    std::memcpy(host.data() + off_bheads, p.fwd.block_heads.data(), p.fwd.block_heads.size() * sizeof(int32_t));
 
   hipError_t e = hipGetDevice(&p.device);
   if (e != hipSuccess) return device_fail(e, "hipGetDevice");
@@ -136,6 +148,10 @@ fdmt_status_t upload(fdmt::Plan &p) {
   p.dev_adj_order = reinterpret_cast<const int32_t *>(base + off_adj_order);
   p.dev_sterms = reinterpret_cast<const int2 *>(base + off_sterms);
   p.dev_sheads = reinterpret_cast<const int32_t *>(base + off_sheads);
+  p.dev_block_iplaces = reinterpret_cast<const int4 *>(base + off_biplaces);
+  p.dev_block_places = reinterpret_cast<const int2 *>(base + off_bplaces);
+  p.dev_block_offs = reinterpret_cast<const int32_t *>(base + off_boffs);
+  p.dev_block_heads = reinterpret_cast<const int32_t *>(base + off_bheads);
   e = fdmt::prepare_kernels(p);
   if (e != hipSuccess) return device_fail(e, "hipFuncSetAttribute (dynamic LDS)");
   return FDMT_OK;
@@ -300,8 +316,21 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
     // the d_min pre-shift rides on the input terms of a gather from the input
     else if (o.d_min > 0) sp.first_kind = fdmt::PassKind::Register;
     if (o.later_kernel) sp.later_kind = kinds[o.later_kernel];
+    // Block passes (fdmt_block.hip) are the default: at every shape measured
+    // they beat the other forms, also the tuned register gathers, from Nf=64,
+    // Nt=1024 (8 us against 23 us) to Nf=4096, Nt=65536 (0.61 ms against 0.78 ms,
+    // uint8). A nonzero forward schedule field asks for another form, and these
+    // also run what block passes do not cover: fewer than three iterations,
+    // block shifts that spread past half a tile, or an Nt with more block tiles
+    // than the grid's y dimension holds.
+    const bool open = !o.first_levels && !o.later_levels && !o.tile && !o.lds_kib && !o.max_block_rows &&
+                      !o.first_kernel && !o.later_kernel && !o.stream_tiles && !o.gather_rows && !o.gather_threads &&
+                      !o.first_rows && !o.first_threads;
     try {
-      const std::string err = fdmt::build_schedule(p.fwd, p.tab, sp);
+      bool block = open && fdmt::build_block_schedule(p.fwd, p.tab, nt, o.search_rows > 0).empty();
+      for (const fdmt::Pass &ps : p.fwd.passes)
+        if (block && ps.kind == fdmt::PassKind::Block && (nt + ps.tile - 1) / ps.tile > 65535) block = false;
+      const std::string err = block ? "" : fdmt::build_schedule(p.fwd, p.tab, sp);
       if (!err.empty()) {
         delete h;
         return fail(FDMT_E_UNSUPPORTED, "schedule: " + err);
@@ -334,7 +363,8 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
   if (o.in_dtype == FDMT_U8 && !(o.flags & FDMT_PLAN_WIDE_PLANES)) {
     for (size_t i = 0; i + 1 < p.fwd.passes.size(); ++i) {
       const fdmt::Pass &a = p.fwd.passes[i], &b = p.fwd.passes[i + 1];
-      if (!a.gather || !b.gather || b.from_input) continue;
+      const bool sums = (a.gather || a.kind == fdmt::PassKind::Block) && (b.gather || b.kind == fdmt::PassKind::Block);
+      if (!sums || b.from_input) continue;
       if (!a.from_input && !(i > 0 && p.narrow[i - 1])) continue;
       int64_t rows = 0;
       for (int32_t r : p.tab.rows[a.l1]) rows = std::max<int64_t>(rows, r);
@@ -347,13 +377,46 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
   p.int_sums.assign(p.fwd.passes.size(), 0);
   for (size_t i = 0; i < p.fwd.passes.size(); ++i) {
     const fdmt::Pass &a = p.fwd.passes[i];
-    if (!a.gather) continue;
+    if (!a.gather && a.kind != fdmt::PassKind::Block) continue;
     if (!(a.from_input ? o.in_dtype == FDMT_U8 : i > 0 && p.narrow[i - 1])) continue;
     int64_t rows = 0;
     for (int32_t r : p.tab.rows[a.l1]) rows = std::max<int64_t>(rows, r);
     if (o.acc_dtype == FDMT_I32 || 255 * ((int64_t(1) << a.l1) + rows - 1) < (int64_t(1) << 24)) p.int_sums[i] = 1;
   }
-  p.pad_input = p.tab.slots != p.tab.nf;
+  // Where the terms of block passes lie in a uniform batch's buffers.
+  try {
+    for (size_t i = 0; i < p.fwd.passes.size(); ++i) {
+      const fdmt::Pass &ps = p.fwd.passes[i];
+      if (ps.kind != fdmt::PassKind::Block) continue;
+      const auto place = [](int64_t at, int32_t &lo, int32_t &hi) {
+        lo = static_cast<int32_t>(static_cast<uint32_t>(at));
+        hi = static_cast<int32_t>(at >> 32);
+      };
+      if (ps.from_input) {
+        const int64_t eb = o.in_dtype == FDMT_U8 ? 1 : o.in_dtype == FDMT_F16 ? 2 : 4;
+        for (const fdmt::InTerm &x : p.fwd.iterms) {
+          fdmt::InTerm y = x;
+          place((x.ch * nt - x.shift) * eb, y.ch, y.shift);
+          y.pad = 0;
+          y.chain = x.chain;
+          p.block_iplaces.push_back(y);
+        }
+      } else {
+        const int64_t eb = i > 0 && p.narrow[i - 1] ? 2 : 4;
+        p.block_places.resize(p.fwd.terms.size());
+        for (int64_t j = ps.term_offset; j < ps.term_offset + ps.term_count; ++j) {
+          const fdmt::Term x = p.fwd.terms[j];
+          place((x.row * p.ntp - x.shift) * eb, p.block_places[j].row, p.block_places[j].shift);
+        }
+      }
+    }
+  } catch (const std::bad_alloc &) {
+    delete h;
+    return fail(FDMT_E_NOMEM, "host allocation of the schedule failed");
+  }
+  // block passes from the input know which channel positions hold no channel
+  p.pad_input = p.tab.slots != p.tab.nf &&
+                !(!p.fwd.passes.empty() && p.fwd.passes[0].kind == fdmt::PassKind::Block && p.fwd.passes[0].from_input);
   fdmt::plan_steps(p);
   // Time tiles of uniform batches run along the grid's y dimension (at most
   // 65535 workgroups).
@@ -492,18 +555,21 @@ fdmt_status_t fdmt_step_info(fdmt_plan_t p, int32_t adjoint, int32_t step, fdmt_
       break;
     case fdmt::Step::Fused: {
       const fdmt::Pass &ps = P.fwd.passes[st.index];
-      info->kind = ps.kind == fdmt::PassKind::Staged ? 7 : !ps.gather ? 2 : ps.from_input ? 6 : 5;
+      const bool block = ps.kind == fdmt::PassKind::Block;
+      info->kind = ps.kind == fdmt::PassKind::Staged ? 7 : !ps.gather && !block ? 2 : ps.from_input ? 6 : 5;
       info->level_first = ps.from_input ? 0 : ps.l0 + 1;
       info->level_last = ps.l1;
       const int64_t gt = fdmt::step_tile(P, false, step);  // samples per gather workgroup
       const int rows = fdmt::forward_rows(P, ps);
-      info->work_items = ps.gather ? static_cast<int32_t>(((ps.nblocks + rows - 1) / rows) * ((nt + gt - 1) / gt))
+      info->work_items = block ? static_cast<int32_t>(ps.nblocks * ((nt + gt - 1) / gt))
+                         : ps.gather ? static_cast<int32_t>(((ps.nblocks + rows - 1) / rows) * ((nt + gt - 1) / gt))
                                    : static_cast<int32_t>(
                                          ps.nblocks *
                                          ((nt + ps.tile - 1) / ps.tile +
                                           (ps.kind == fdmt::PassKind::Staged ? P.tiles_per_wg : P.rec_tiles) - 1) /
                                          (ps.kind == fdmt::PassKind::Staged ? P.tiles_per_wg : P.rec_tiles));
       info->lds_bytes = ps.gather ? 0
+                        : block ? static_cast<int64_t>(fdmt::block_lds_bytes(ps))
                         : ps.kind == fdmt::PassKind::Staged
                             ? static_cast<int64_t>(ps.lds_a + ps.lds_p + ps.lds_b + ps.max_recs) * 4
                             : static_cast<int64_t>(ps.lds_a + ps.lds_b + 2 * fdmt::kLdsSlack) * 4;

@@ -811,6 +811,36 @@ hipError_t run_forward_step(const Plan &p, const Step &st, const void *in, void 
                                                  ps.nblocks);
         });
       }
+      if (ps.kind == PassKind::Block) {
+        const bool narrow_in = st.index > 0 && p.narrow[st.index - 1];
+        const bool narrow_out = p.narrow[st.index];
+        const bool int_sums = p.int_sums[st.index];
+        return for_each_launch(p, rb, st, false, ps.tile * ps.tiles_per_wg, batch, [&](auto r, unsigned gy, unsigned gz, const RaggedMap &rg) {
+          BlockLaunch g{dim3(static_cast<unsigned>(ps.nblocks), gy, gz), stream, rg, decltype(r)::value,
+                        st.dst == Buf::Out, &ps,
+                        ps.from_input ? static_cast<const void *>(p.dev_iterms + ps.term_offset)
+                                      : static_cast<const void *>(p.dev_terms + ps.term_offset),
+                        ps.from_input ? static_cast<const void *>(p.dev_block_iplaces + ps.term_offset)
+                                      : static_cast<const void *>(p.dev_block_places + ps.term_offset),
+                        p.dev_block_offs + ps.offs_offset, p.dev_block_heads + ps.head_offset,
+                        static_cast<int32_t>(nt), src.stride, src.bstride, dst.stride, dst.bstride};
+          if (ps.from_input) {
+            const Tin *sp = static_cast<const Tin *>(src.ptr);
+            if constexpr (std::is_same<Tin, uint8_t>::value) {
+              if (narrow_out) return launch_block<uint8_t, int32_t, uint16_t, true>(g, sp, static_cast<uint16_t *>(dst.ptr));
+              if (int_sums) return launch_block<uint8_t, int32_t, Tacc, true>(g, sp, static_cast<Tacc *>(dst.ptr));
+            }
+            return launch_block<Tin, Tacc, Tacc, true>(g, sp, static_cast<Tacc *>(dst.ptr));
+          }
+          if (narrow_in) {
+            const uint16_t *sp = static_cast<const uint16_t *>(src.ptr);
+            if (narrow_out) return launch_block<uint16_t, int32_t, uint16_t, false>(g, sp, static_cast<uint16_t *>(dst.ptr));
+            return launch_block<uint16_t, int32_t, Tacc, false>(g, sp, static_cast<Tacc *>(dst.ptr));
+          }
+          if (narrow_out) return hipErrorInvalidValue;  // narrow planes are made from narrow planes
+          return launch_block<Tacc, Tacc, Tacc, false>(g, static_cast<const Tacc *>(src.ptr), static_cast<Tacc *>(dst.ptr));
+        });
+      }
       FusedArgs a{};
       a.src = src.ptr;
       a.dst = dst.ptr;
@@ -1001,7 +1031,7 @@ hipError_t set_staged_lds(int lds) {
 hipError_t prepare_kernels(const Plan &p) {
   size_t lds = 0;
   for (const Pass &ps : p.fwd.passes)
-    if (!ps.gather) lds = std::max(lds, fused_lds_bytes(ps));
+    if (!ps.gather && ps.kind != PassKind::Block) lds = std::max(lds, fused_lds_bytes(ps));
   if (lds <= 64 * 1024) return hipSuccess;
   const void *fns[] = {
 #define FDMT_FUSED_ALL(R)                                                                   \
@@ -1162,6 +1192,7 @@ int step_tile(const Plan &p, bool adjoint, int i) {
     case Step::Fused: {
       const Pass &ps = p.fwd.passes[st.index];
       if (ps.kind == PassKind::Staged) return 0;
+      if (ps.kind == PassKind::Block) return ps.tile * ps.tiles_per_wg;
       return ps.gather ? 256 * forward_vecs(p, ps) * (forward_threads(p, ps) / 64 / forward_rows(p, ps))
                        : ps.tile * p.rec_tiles;
     }

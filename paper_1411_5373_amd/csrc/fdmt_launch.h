@@ -75,6 +75,23 @@ hipError_t launch_narrow_gather(const GatherLaunch &g, const uint16_t *src, Tdst
                                 int32_t nt, int64_t src_stride, int64_t src_bstride, int64_t dst_stride,
                                 int64_t dst_bstride, int32_t nrows);
 
+// One launch of a block pass (see kBlockPitch).
+struct BlockLaunch {
+  dim3 grid;  // blocks, time tiles, beams
+  hipStream_t stream;
+  RaggedMap rg;
+  bool ragged, streaming;
+  const Pass *pass;
+  const void *terms;            // the pass's Term (InTerm) records on the device
+  const void *places;           // the same with byte offsets (see Plan::block_places)
+  const int32_t *offs, *heads;  // its LDS offsets and block headers
+  int32_t nt;
+  int64_t src_stride, src_bstride, dst_stride, dst_bstride;
+};
+size_t block_lds_bytes(const Pass &ps);
+template <typename Tsrc, typename Tacc, typename Tdst, bool FROM_INPUT>
+hipError_t launch_block(const BlockLaunch &g, const Tsrc *src, Tdst *dst);
+
 // Adjoint register gather over a depth-first leaf list; max_shift bounds the
 // shifts of every leaf.
 template <typename Tacc>

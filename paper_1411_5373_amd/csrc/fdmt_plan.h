@@ -78,6 +78,15 @@ struct Plan {
   uint32_t adjoint_tile_major = 0;  // bit i: adjoint pass i runs each row group's tiles back to back
   const int2 *dev_sterms = nullptr;
   const int32_t *dev_sheads = nullptr;
+  // Block passes, uniform batches: per stage-1 term (in Schedule::iterms or
+  // ::terms order, each pass by its own strides) the byte offset of sample
+  // -shift of its row, low and high word, then the chain of an input term.
+  std::vector<InTerm> block_iplaces;
+  std::vector<Term> block_places;
+  const int4 *dev_block_iplaces = nullptr;
+  const int2 *dev_block_places = nullptr;
+  const int32_t *dev_block_offs = nullptr;
+  const int32_t *dev_block_heads = nullptr;
   std::vector<uint8_t> narrow; // per forward pass: its output plane holds uint16 sums
   std::vector<uint8_t> int_sums; // per forward pass: uint8 input or uint16 planes in, sums integers below 2^24
   std::vector<Step> fwd_steps, adj_steps;

@@ -557,6 +557,212 @@ std::string build_schedule(Schedule &s, const Tables &t, const ScheduleParams &p
 
 namespace {
 
+// How a block pass of k iterations splits over its stages: two iterations
+// loaded through the caches, at most three from LDS at a time.
+struct BlockSplit {
+  int k1, k2, k3;
+};
+BlockSplit block_split(int k) {
+  switch (k) {
+    case 3: return {1, 0, 2};
+    case 4: return {2, 0, 2};
+    case 5: return {2, 0, 3};
+    default: return {2, 2, 2};
+  }
+}
+
+// The 2^k terms of row `row` of plane l, k iterations down, in the order the
+// recursion adds them.
+void walk_terms(const Tables &t, int l, int k, int64_t row, std::vector<Term> &cur, std::vector<Term> &tmp) {
+  cur.assign(1, Term{static_cast<int32_t>(row), 0});
+  for (int i = 0; i < k; ++i, --l) {
+    tmp.clear();
+    for (const Term &x : cur) {
+      const MergeRow &m = t.merge[l][x.row];
+      tmp.push_back(Term{m.lo, x.shift});
+      tmp.push_back(Term{m.hi, x.shift + m.s});
+    }
+    cur.swap(tmp);
+  }
+}
+
+// LDS offsets of the rows of `tops` (nodes k levels above `leaves`, which lie
+// in LDS from row base[i] on): appended to offs, in row order.
+std::string block_offsets(const Tables &t, int l, int k, const Node *tops, int ntops, const Node *leaves,
+                          const std::vector<int> &base, int lead, int tile, std::vector<int32_t> &offs) {
+  std::vector<Term> cur, tmp;
+  for (int j = 0; j < ntops; ++j) {
+    const Node &n = tops[j];
+    for (int r = 0; r < n.nrows; ++r) {
+      walk_terms(t, l, k, n.row0 + r, cur, tmp);
+      for (size_t q = 0; q < cur.size(); ++q) {
+        const size_t i = static_cast<size_t>(j) * cur.size() + q;
+        const Node &x = leaves[i];
+        const int rl = cur[q].row - x.row0;
+        if (rl < 0 || rl >= x.nrows) return "block term row outside its node";
+        const int col = lead + x.win - n.win - cur[q].shift;  // column of the top row's first sample
+        if (col < lead || col + n.width > lead + x.width || lead + x.width + tile > kBlockPitch - kBlockTail) return "block term window";
+        offs.push_back((base[i] + rl) * kBlockPitch + col);
+      }
+    }
+  }
+  return "";
+}
+
+std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, int k, bool from_input) {
+  Pass ps;
+  ps.kind = PassKind::Block;
+  ps.from_input = from_input;
+  ps.l0 = l0;
+  ps.l1 = l0 + k;
+  const BlockSplit sp = block_split(k);
+  ps.k1 = sp.k1;
+  ps.k2 = sp.k2;
+  ps.k3 = sp.k3;
+  ps.rows_in = from_input ? t.slots : t.total[l0];
+  ps.rows_out = t.total[ps.l1];
+  ps.term_offset = static_cast<int64_t>(from_input ? s.iterms.size() : s.terms.size());
+  ps.offs_offset = static_cast<int64_t>(s.block_offs.size());
+  ps.head_offset = static_cast<int64_t>(s.block_heads.size());
+  std::vector<int32_t> channel_of;
+  if (from_input) {
+    channel_of.resize(t.total[0]);
+    for (int ch = 0; ch < t.slots; ++ch)
+      for (int d = 0; d < t.leaf_rows[ch]; ++d) channel_of[t.leaf_off[ch] + d] = ch;
+  }
+  // Blocks of at most max_rows rows, each sub-band's rows split evenly.
+  int max_rows = k == 6 ? 16 : 18;
+  const int64_t tiles = (nt + kBlockPitch - 33) / (kBlockPitch - 32);
+  const auto count_blocks = [&]() {
+    int64_t n = 0;
+    for (int32_t r : t.rows[ps.l1]) n += (r + max_rows - 1) / max_rows;
+    return n;
+  };
+  while (max_rows > 4 && count_blocks() * tiles < 256) max_rows /= 2;
+  // A node's width with a tile of 0 samples is the spread of its shifts.
+  struct Range {
+    int sub, r0, nr;
+    Tree tree;
+  };
+  std::vector<Range> blocks;
+  int spread = 0;
+  for (int sub = 0; sub < (t.slots >> ps.l1); ++sub) {
+    const int n = t.rows[ps.l1][sub];
+    const int nb = (n + max_rows - 1) / max_rows;
+    for (int b = 0; b < nb; ++b) {
+      const int r0 = static_cast<int>(static_cast<int64_t>(n) * b / nb);
+      const int r1 = static_cast<int>(static_cast<int64_t>(n) * (b + 1) / nb);
+      blocks.push_back({sub, r0, r1 - r0, build_tree(t, false, l0, ps.l1, sub, r0, r1 - r0, 0)});
+      const Tree &tr = blocks.back().tree;
+      // nodes level by level, leaves first: the nodes of level i start at 2^(k+1) - 2^(k+1-i)
+      for (size_t j = (2u << k) - (2u << (k - ps.k1)); j < tr.nodes.size(); ++j) spread = std::max(spread, tr.nodes[j].width);
+    }
+  }
+  const int lead = from_input ? kBlockLead : 0;
+  ps.tile = (kBlockPitch - kBlockTail - spread - lead) / 32 * 32;
+  if (ps.tile < 128) return "block shifts spread too far";
+  if (from_input && static_cast<int64_t>(blocks.size()) * ((nt + ps.tile - 1) / ps.tile) >= 4096) ps.tiles_per_wg = 2;
+  std::vector<Term> cur, tmp;
+  std::vector<int> base_a, base_b;
+  for (const Range &b : blocks) {
+    const auto level = [&](int i) { return b.tree.nodes.data() + ((2 << k) - (2 << (k - i))); };
+    const auto bases = [](const Node *n, int count, std::vector<int> &base) {
+      int rows = 0;
+      base.resize(count);
+      for (int j = 0; j < count; ++j) {
+        base[j] = rows;
+        rows += n[j].nrows;
+      }
+      return rows;
+    };
+    int32_t head[kBlockHeader] = {};
+    head[0] = static_cast<int32_t>((from_input ? s.iterms.size() : s.terms.size()) - ps.term_offset);
+    // stage 1: the rows of area A, each term's shift counted from the row's column 0
+    const Node *na = level(ps.k1);
+    const int count_a = 1 << (k - ps.k1);
+    const int rows_a = bases(na, count_a, base_a);
+    int reach = 0;
+    for (int j = 0; j < count_a; ++j) {
+      for (int r = 0; r < na[j].nrows; ++r) {
+        walk_terms(t, l0 + ps.k1, ps.k1, na[j].row0 + r, cur, tmp);
+        for (const Term &x : cur) {
+          if (x.row < 0 || x.row >= t.total[l0] || x.shift < 0) return "block term out of range";
+          const int shift = x.shift + na[j].win + lead;
+          if (from_input) {
+            const int ch = channel_of[x.row];
+            const int d = x.row - t.leaf_off[ch];
+            // a position without a channel: past the start of every record, so zero
+            s.iterms.push_back(ch < t.nf ? InTerm{ch, shift + t.pre[ch], d, 0} : InTerm{0, kNoChannelPre, 0, 0});
+            reach = std::max(reach, s.iterms.back().shift);
+            ps.staged_rows += d + 1;
+            ps.max_chain = std::max(ps.max_chain, d);
+          } else {
+            s.terms.push_back(Term{x.row, shift});
+            reach = std::max(reach, shift);
+            ++ps.staged_rows;
+          }
+        }
+      }
+    }
+    head[1] = rows_a;
+    head[7] = reach;
+    head[2] = static_cast<int32_t>(s.block_offs.size() - ps.offs_offset);
+    const Node *below = na;
+    std::vector<int> *base = &base_a;
+    int rows_b = 0;
+    std::string err;
+    if (ps.k2 > 0) {
+      const Node *nb = level(ps.k1 + ps.k2);
+      const int count_b = 1 << ps.k3;
+      rows_b = bases(nb, count_b, base_b);
+      err = block_offsets(t, l0 + ps.k1 + ps.k2, ps.k2, nb, count_b, na, base_a, lead, ps.tile, s.block_offs);
+      if (!err.empty()) return err;
+      below = nb;
+      base = &base_b;
+    }
+    head[3] = rows_b;
+    head[4] = static_cast<int32_t>(s.block_offs.size() - ps.offs_offset);
+    err = block_offsets(t, ps.l1, ps.k3, level(k), 1, below, *base, ps.k2 > 0 ? 0 : lead, ps.tile, s.block_offs);
+    if (!err.empty()) return err;
+    head[5] = b.nr;
+    head[6] = static_cast<int32_t>(t.row_off[ps.l1][b.sub] + b.r0);
+    s.block_heads.insert(s.block_heads.end(), head, head + kBlockHeader);
+    ps.rows_a = std::max(ps.rows_a, rows_a);
+    ps.rows_b = std::max(ps.rows_b, rows_b);
+  }
+  if ((ps.rows_a + ps.rows_b + 1) * kBlockPitch * 4 > 64 * 1024) return "block rows do not fit LDS";
+  ps.nblocks = static_cast<int>(blocks.size());
+  ps.term_count = static_cast<int64_t>(from_input ? s.iterms.size() : s.terms.size()) - ps.term_offset;
+  s.passes.push_back(ps);
+  return "";
+}
+
+} // namespace
+
+std::string build_block_schedule(Schedule &s, const Tables &t, int64_t nt, bool search) {
+  s = Schedule();
+  const int L = search ? t.levels - 3 : t.levels;  // iterations of the block passes
+  if (L < 3) return "fewer than three iterations";
+  int chain = 0;
+  for (int k = 0; k < t.nf; ++k) chain = std::max(chain, t.leaf_rows[k] - 1);
+  s.init_separate = chain > kBlockMaxChain;
+  const int passes = (L + kBlockLevels - 1) / kBlockLevels;
+  int l0 = 0;
+  for (int i = 0; i < passes; ++i) {
+    const int k = (L - l0 + passes - i - 1) / (passes - i);
+    const std::string err = build_block_pass(s, t, nt, l0, k, i == 0 && !s.init_separate);
+    if (!err.empty()) return err;
+    l0 += k;
+  }
+  if (search) {
+    ScheduleParams p;
+    return build_pass(s, t, p, l0, 3, false);
+  }
+  return "";
+}
+
+namespace {
+
 // Depth-first walk of one adjoint output row (see AdjLeaf).
 struct AdjWalker {
   const Tables &t;

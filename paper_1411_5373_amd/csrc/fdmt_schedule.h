@@ -45,7 +45,8 @@ constexpr int kLdsSlack = 64;
 enum class PassKind {
   Staged,     // leaves staged in LDS once, each output the tree sum of its 2^k terms
   Recursive,  // leaves staged in LDS, iterations merged level by level in LDS
-  Register    // each output the tree sum of its 2^k terms loaded through the caches
+  Register,   // each output the tree sum of its 2^k terms loaded through the caches
+  Block       // a block of rows at a time: k1 iterations loaded through the caches into LDS, the others from LDS
 };
 
 // A term of a staged pass: LDS offset of the term's sample at the block's
@@ -84,7 +85,37 @@ struct Pass {
   int lds_p = 0;            // staged first pass: LDS elements of the partial-sum rows
   int stage_ints = 0;       // staged: LDS ints of the staging-record area
   int max_chain = 0;        // register pass from the input: longest Option-1 chain of its terms
+  int k1 = 0, k2 = 0, k3 = 0;  // Block: iterations of its three stages (k1 + k2 + k3 = l1 - l0, k2 may be 0)
+  int rows_a = 0, rows_b = 0;  // Block: most LDS rows of any block after stage 1 and stage 2
+  int tiles_per_wg = 1;        // Block: consecutive time tiles of a workgroup
+  int64_t term_count = 0;      // Block: stage-1 terms of the pass
+  int64_t offs_offset = 0;     // Block: first LDS offset in Schedule::block_offs (heads: head_offset)
 };
+
+// Block passes. A work item is a range of consecutive rows of one sub-band of
+// plane l1 over one time tile [T0, T0 + tile). Its tree (the rows each
+// iteration must supply) is cut at two levels:
+//   stage 1: each row of the block's nodes at level l0 + k1, the tree sum of
+//            its 2^k1 terms of plane l0 (or the input), into LDS area A;
+//   stage 2: (k2 > 0) each row of its nodes at level l0 + k1 + k2, from 2^k2
+//            rows of A, into LDS area B;
+//   stage 3: each output row, from 2^k3 rows of B (of A when k2 = 0).
+// Every LDS row holds kBlockPitch samples: column c of a row of a node whose
+// window is `win` is time T0 - win + c. Columns past the node's own width are
+// computed too and never used.
+constexpr int kBlockPitch = 256;
+// Columns at the start of a row of area A that a pass from the input does not
+// use: the samples its Option-1 chains reach back over.
+constexpr int kBlockLead = 4;
+// Columns at the end of a row of area A that no pass uses: loads of narrow
+// types take the samples past a lane's words from the next lane.
+constexpr int kBlockTail = 4;
+// Per block: [0] first stage-1 term (pass-relative), [1] rows of A, [2] first
+// stage-2 offset, [3] rows of B, [4] first stage-3 offset, [5] output rows,
+// [6] first output row (plane l1), [7] largest shift of its stage-1 terms.
+constexpr int kBlockHeader = 8;
+constexpr int kBlockLevels = 6;    // most iterations of a block pass
+constexpr int kBlockMaxChain = kBlockLead;  // longest Option-1 chain a first pass from the input adds up itself
 
 struct ScheduleParams {
   int first_levels = 4;      // iterations fused with the initialisation
@@ -124,10 +155,18 @@ struct Schedule {
                                 // b = LDS of the staged input row, c = last partial-sum row,
                                 // d = partial-sum row stride, e = width, f = input columns ahead
   std::vector<int32_t> sheads;  // staged passes: kStagedHeader per block
+  std::vector<int32_t> block_offs;   // block passes: LDS offsets of stage 2 and 3 terms
+  std::vector<int32_t> block_heads;  // block passes: kBlockHeader per block
 };
 
 // Builds the pass list and every block's node tree. Returns "" on success.
 std::string build_schedule(Schedule &s, const Tables &t, const ScheduleParams &p);
+
+// The schedule of block passes (see kBlockPitch) for records of nt samples.
+// With `search` the last three iterations are a register gather, the form that
+// can run the boxcar search. Returns "" on success, else why the tables do not
+// suit it.
+std::string build_block_schedule(Schedule &s, const Tables &t, int64_t nt, bool search);
 
 // ---------------------------------------------------------------------------
 // Adjoint schedule. Each pass maps plane l_hi (the gradient of the output when
