@@ -906,7 +906,7 @@ fdmt_status_t fdmt_forward_search(fdmt_plan_t p, const void *in, void *out, int3
     e = fdmt::launch_forward(P, in, out, batch, ws, stream);
     if (e == hipSuccess) e = fdmt::launch_boxcar_tiles(plane, batch, P.tab.nd, P.nt, max_log2, part, stream);
   }
-  if (e == hipSuccess) e = fdmt::launch_boxcar_combine(part, batch, P.tab.nd, P.nt, max_log2, stats, mean_sd, stream);
+  if (e == hipSuccess) e = fdmt::launch_boxcar_combine(part, batch, P.tab.nd, P.nt, max_log2, stats, mean_sd, count, stream);
   if (e == hipSuccess)
     e = fdmt::launch_boxcar_candidates(part, mean_sd, batch, P.tab.nd, P.nt, max_log2, threshold, cands, cap, count,
                                        stream);
