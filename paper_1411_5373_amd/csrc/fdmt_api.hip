@@ -76,6 +76,12 @@ fdmt_status_t upload(fdmt::Plan &p) {
   const size_t off_adj_order = reserve(p.adj.order.size() * sizeof(int32_t));
   const size_t off_sterms = reserve(p.fwd.sterms.size() * sizeof(fdmt::StagedTerm));
   const size_t off_sheads = reserve(p.fwd.sheads.size() * sizeof(int32_t));
+  const size_t off_adj_leaves1 = reserve(p.adj.block_leaves1.size() * sizeof(fdmt::AdjBlockLeaf));
+  const size_t off_adj_places = reserve(p.adj_places.size() * sizeof(fdmt::AdjBlockLeaf));
+  const size_t off_adj_mids = reserve(p.adj.block_mids.size() * sizeof(int32_t));
+  const size_t off_adj_outs = reserve(p.adj.block_outs.size() * sizeof(fdmt::AdjBlockOut));
+  const size_t off_adj_leaves2 = reserve(p.adj.block_leaves2.size() * sizeof(int32_t));
+  const size_t off_adj_heads = reserve(p.adj.block_heads.size() * sizeof(int32_t));
   const size_t off_biplaces = reserve(p.block_iplaces.size() * sizeof(fdmt::InTerm));
   const size_t off_bplaces = reserve(p.block_places.size() * sizeof(fdmt::Term));
   const size_t off_boffs = reserve(p.fwd.block_offs.size() * sizeof(int32_t));
@@ -111,6 +117,12 @@ fdmt_status_t upload(fdmt::Plan &p) {
     std::memcpy(host.data() + off_sterms, p.fwd.sterms.data(), p.fwd.sterms.size() * sizeof(fdmt::StagedTerm));
   if (!p.fwd.sheads.empty())
     std::memcpy(host.data() + off_sheads, p.fwd.sheads.data(), p.fwd.sheads.size() * sizeof(int32_t));
+  if (!p.adj.block_leaves1.empty()) std::memcpy(host.data() + off_adj_leaves1, p.adj.block_leaves1.data(), p.adj.block_leaves1.size() * sizeof(fdmt::AdjBlockLeaf));
+  if (!p.adj_places.empty()) std::memcpy(host.data() + off_adj_places, p.adj_places.data(), p.adj_places.size() * sizeof(fdmt::AdjBlockLeaf));
+  if (!p.adj.block_mids.empty()) std::memcpy(host.data() + off_adj_mids, p.adj.block_mids.data(), p.adj.block_mids.size() * sizeof(int32_t));
+  if (!p.adj.block_outs.empty()) std::memcpy(host.data() + off_adj_outs, p.adj.block_outs.data(), p.adj.block_outs.size() * sizeof(fdmt::AdjBlockOut));
+  if (!p.adj.block_leaves2.empty()) std::memcpy(host.data() + off_adj_leaves2, p.adj.block_leaves2.data(), p.adj.block_leaves2.size() * sizeof(int32_t));
+  if (!p.adj.block_heads.empty()) std::memcpy(host.data() + off_adj_heads, p.adj.block_heads.data(), p.adj.block_heads.size() * sizeof(int32_t));
   if (!p.block_iplaces.empty())
     std::memcpy(host.data() + off_biplaces, p.block_iplaces.data(), p.block_iplaces.size() * sizeof(fdmt::InTerm));
   if (!p.block_places.empty())
@@ -148,6 +160,12 @@ fdmt_status_t upload(fdmt::Plan &p) {
   p.dev_adj_order = reinterpret_cast<const int32_t *>(base + off_adj_order);
   p.dev_sterms = reinterpret_cast<const int2 *>(base + off_sterms);
   p.dev_sheads = reinterpret_cast<const int32_t *>(base + off_sheads);
+  p.dev_adj_leaves1 = reinterpret_cast<const fdmt::AdjBlockLeaf *>(base + off_adj_leaves1);
+  p.dev_adj_places = reinterpret_cast<const fdmt::AdjBlockLeaf *>(base + off_adj_places);
+  p.dev_adj_mids = reinterpret_cast<const int32_t *>(base + off_adj_mids);
+  p.dev_adj_outs = reinterpret_cast<const fdmt::AdjBlockOut *>(base + off_adj_outs);
+  p.dev_adj_leaves2 = reinterpret_cast<const int32_t *>(base + off_adj_leaves2);
+  p.dev_adj_heads = reinterpret_cast<const int32_t *>(base + off_adj_heads);
   p.dev_block_iplaces = reinterpret_cast<const int4 *>(base + off_biplaces);
   p.dev_block_places = reinterpret_cast<const int2 *>(base + off_bplaces);
   p.dev_block_offs = reinterpret_cast<const int32_t *>(base + off_boffs);
@@ -344,7 +362,18 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
     try {
       const int per = o.adjoint_levels ? o.adjoint_levels : 2;
       const int last = o.adjoint_last_levels ? o.adjoint_last_levels : 2;
-      const std::string err = fdmt::build_adjoint_schedule(p.adj, p.tab, per, last);
+      // Block passes (fdmt_adjoint_block.hip) unless an adjoint or gather field
+      // asks for the register gathers: faster from Nf=64, Nt=1024 (11.5 us against
+      // 16.8 us) to Nf=4096, Nt=65536 (1.05 ms against 1.33 ms tuned). The register
+      // gathers also run what block passes do not cover: fewer than two iterations,
+      // shifts that spread past 128 samples in a block, an Nt with too many tiles.
+      const bool open = !o.adjoint_levels && !o.adjoint_last_levels && !o.adjoint_last_rows && !o.adjoint_rows &&
+                        !o.adjoint_tile_major && !o.adjoint_threads && !o.adjoint_last_threads && !o.gather_rows &&
+                        !o.gather_vecs;
+      bool block = open && fdmt::build_adjoint_block_schedule(p.adj, p.tab, nt).empty();
+      for (const fdmt::AdjPass &ps : p.adj.passes)
+        if (block && (nt + ps.extra + ps.tile - 1) / ps.tile > 65535) block = false;
+      const std::string err = block ? "" : fdmt::build_adjoint_schedule(p.adj, p.tab, per, last);
       if (!err.empty()) {
         delete h;
         return fail(FDMT_E_UNSUPPORTED, "adjoint schedule: " + err);
@@ -385,6 +414,15 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
   }
   // Where the terms of block passes lie in a uniform batch's buffers.
   try {
+    p.adj_places.resize(p.adj.block_leaves1.size());
+    for (size_t i = 0; i < p.adj.passes.size(); ++i) {
+      const fdmt::AdjPass &ps = p.adj.passes[i];
+      for (int64_t j = ps.leaf_offset; ps.block && j < ps.leaf_offset + ps.leaf1_count; ++j) {
+        const fdmt::AdjBlockLeaf &x = p.adj.block_leaves1[j];
+        const int64_t at = (x.row * (i == 0 ? nt : p.ntp) + (x.shift4 >> 2)) * 4 + (x.shift4 & 3);
+        p.adj_places[j] = {static_cast<int32_t>(static_cast<uint32_t>(at)), static_cast<int32_t>(at >> 32)};
+      }
+    }
     for (size_t i = 0; i < p.fwd.passes.size(); ++i) {
       const fdmt::Pass &ps = p.fwd.passes[i];
       if (ps.kind != fdmt::PassKind::Block) continue;
@@ -598,9 +636,14 @@ fdmt_status_t fdmt_step_info(fdmt_plan_t p, int32_t adjoint, int32_t step, fdmt_
       info->kind = 8;
       info->level_first = ps.to_input ? 0 : ps.l_lo + 1;
       info->level_last = ps.l_hi;
-      const int rows = fdmt::adjoint_rows(P, st.index);
       const int64_t tile = fdmt::step_tile(P, true, step);
-      info->work_items = static_cast<int32_t>(((ps.nrows + rows - 1) / rows) * ((nt + tile - 1) / tile));
+      if (ps.block) {
+        info->work_items = static_cast<int32_t>(ps.nblocks * ((nt + ps.extra + tile - 1) / tile));
+        info->lds_bytes = static_cast<int64_t>(fdmt::adjoint_block_lds_bytes(ps));
+      } else {
+        const int rows = fdmt::adjoint_rows(P, st.index);
+        info->work_items = static_cast<int32_t>(((ps.nrows + rows - 1) / rows) * ((nt + tile - 1) / tile));
+      }
       info->bytes_read = T.total[ps.l_hi] * nt * 4;
       info->bytes_written = static_cast<int64_t>(ps.nrows) * nt * 4;
       info->staged_bytes = ps.leaves * nt * 4;
@@ -693,13 +736,14 @@ fdmt_status_t fdmt_ragged_plan(fdmt_ragged_t *out, fdmt_plan_t p, int32_t nbeams
     if (sump > INT32_MAX) return fail(FDMT_E_UNSUPPORTED, "total samples of the batch exceed 2^31 - 1");
   }
   // Tile widths of every step of both transforms.
-  std::vector<int> widths;
+  std::vector<std::pair<int, int32_t>> widths;  // width, samples covered past a beam's end
   for (int adj = 0; adj < 2; ++adj) {
     const int n = static_cast<int>(adj ? P.adj_steps.size() : P.fwd_steps.size());
     for (int i = 0; i < n; ++i) {
       const int w = fdmt::step_tile(P, adj != 0, i);
       if (w <= 0) return fail(FDMT_E_UNSUPPORTED, "the plan's staged-gather passes have no ragged form");
-      if (std::find(widths.begin(), widths.end(), w) == widths.end()) widths.push_back(w);
+      const std::pair<int, int32_t> key(w, fdmt::step_extra(P, adj != 0, i));
+      if (std::find(widths.begin(), widths.end(), key) == widths.end()) widths.push_back(key);
     }
   }
   if (P.flags & FDMT_PLAN_HOST_ONLY)
@@ -717,7 +761,7 @@ fdmt_status_t fdmt_ragged_plan(fdmt_ragged_t *out, fdmt_plan_t p, int32_t nbeams
       off += nt[b];
       poff += ntp;
       for (size_t m = 0; m < widths.size(); ++m)
-        for (int64_t j = 0; j * widths[m] < nt[b]; ++j) maps[m].push_back(make_int2(b, static_cast<int>(j)));
+        for (int64_t j = 0; nt[b] > 0 && j * widths[m].first < nt[b] + widths[m].second; ++j) maps[m].push_back(make_int2(b, static_cast<int>(j)));
     }
   } catch (const std::bad_alloc &) {
     delete h;
@@ -760,7 +804,7 @@ fdmt_status_t fdmt_ragged_plan(fdmt_ragged_t *out, fdmt_plan_t p, int32_t nbeams
   h->rb.sum_ntp = sump;
   h->rb.beam = reinterpret_cast<const int4 *>(base);
   for (size_t m = 0; m < widths.size(); ++m)
-    h->rb.maps.push_back({widths[m], static_cast<int64_t>(maps[m].size()),
+    h->rb.maps.push_back({widths[m].first, widths[m].second, static_cast<int64_t>(maps[m].size()),
                           reinterpret_cast<const int2 *>(base + map_off[m])});
   *out = h;
   return FDMT_OK;
@@ -814,7 +858,7 @@ fdmt_status_t fdmt_ragged_info(fdmt_ragged_t r, int32_t *nbeams, int64_t *total_
       for (int i = 0; i < k; ++i) {
         const int w = fdmt::step_tile(P, adj != 0, i);
         for (const fdmt::RaggedBatch::Map &m : r->rb.maps)
-          if (m.tile == w) n += static_cast<int32_t>((m.count + 65534) / 65535);
+          if (m.tile == w && m.extra == fdmt::step_extra(P, adj != 0, i)) n += static_cast<int32_t>((m.count + 65534) / 65535);
       }
     }
     *launches = n;

@@ -109,17 +109,6 @@ struct Quad<uint8_t> {
   }
 };
 
-// Tables are read-only for the whole launch and read at wave-uniform places:
-// the constant address space makes them scalar loads.
-template <typename T>
-using Const = const __attribute__((address_space(4))) T *;
-template <typename T>
-__device__ __forceinline__ Const<T> as_const(const void *p) {
-  return reinterpret_cast<Const<T>>(reinterpret_cast<uintptr_t>(p));
-}
-typedef int32_t Int2 __attribute__((ext_vector_type(2)));
-typedef int32_t Int4 __attribute__((ext_vector_type(4)));
-
 struct BlockArgs {
   const void *terms;   // Term (from a plane) or InTerm (from the input) records of the pass
   const void *places;  // uniform batches: the same records, {row, shift} as the byte offset of the term's place

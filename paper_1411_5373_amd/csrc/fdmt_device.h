@@ -95,7 +95,6 @@ __device__ __forceinline__ int xcd_local_order(int id, int n) {
 }
 
 
-
 // Place of a wave in a register-gather workgroup of blockDim.x threads that
 // holds rows_per_wg rows side by side, col_waves waves along time per row.
 // Workgroup sizes and rows per workgroup are powers of two (the launchers
@@ -147,6 +146,17 @@ __device__ __forceinline__ int2 gather_item(int groups, bool tiles_fastest) {
 // for every lane of a wave: reading them through the constant address space
 // makes them scalar loads.
 typedef const __attribute__((address_space(4))) int32_t *ConstInts;
+
+// Tables are read-only for the whole launch and read at wave-uniform places:
+// the constant address space makes them scalar loads.
+template <typename T>
+using Const = const __attribute__((address_space(4))) T *;
+template <typename T>
+__device__ __forceinline__ Const<T> as_const(const void *p) {
+  return reinterpret_cast<Const<T>>(reinterpret_cast<uintptr_t>(p));
+}
+typedef int32_t Int2 __attribute__((ext_vector_type(2)));
+typedef int32_t Int4 __attribute__((ext_vector_type(4)));
 
 // Largest workgroup of the register-gather kernels (their register budget is
 // set for it); a launch may use 64 .. 1024 threads, a power of two.

@@ -616,14 +616,15 @@ inline int forward_vecs(const Plan &p, const Pass &ps) {
   return p.gather_vecs < 2 ? p.gather_vecs : 2;
 }
 
-// Issues the launches of one step over time tiles of width `tile`. A uniform
-// batch is one launch: ceil(nt / tile) tiles in grid y, beams in grid z. A
+// Issues the launches of one step over time tiles of width `tile`, which cover
+// `extra` samples past a record's end. A uniform
+// batch is one launch: ceil((nt + extra) / tile) tiles in grid y, beams in grid z. A
 // ragged batch walks the flattened tile map of that width, at most 65535
 // tiles per launch. `launch(ragged, grid_y, grid_z, map)` issues one launch
 // and returns its status.
 template <typename F>
 hipError_t for_each_launch(const Plan &p, const RaggedBatch *rb, const Step &st, bool adjoint,
-                           int tile, int batch, F &&launch) {
+                           int tile, int batch, F &&launch, int32_t extra = 0) {
   if (rb == nullptr) {
     RaggedMap order{};
     // Consecutive steps run their beams and time tiles in opposite orders, so
@@ -632,13 +633,13 @@ hipError_t for_each_launch(const Plan &p, const RaggedBatch *rb, const Step &st,
     // Nf=4096 step and the batch-16 differentiable step each gained 1.5%.
     const std::vector<Step> &steps = adjoint ? p.adj_steps : p.fwd_steps;
     order.reverse = static_cast<int32_t>((&st - steps.data()) & 1);
-    const hipError_t e = launch(std::false_type{}, static_cast<unsigned>((p.nt + tile - 1) / tile),
+    const hipError_t e = launch(std::false_type{}, static_cast<unsigned>((p.nt + extra + tile - 1) / tile),
                                 static_cast<unsigned>(batch), order);
     return e != hipSuccess ? e : hipGetLastError();
   }
   const RaggedBatch::Map *m = nullptr;
   for (const RaggedBatch::Map &x : rb->maps)
-    if (x.tile == tile) m = &x;
+    if (x.tile == tile && x.extra == extra) m = &x;
   if (m == nullptr) return hipErrorInvalidValue;
   RaggedMap rg{};
   rg.beam = rb->beam;
@@ -893,6 +894,16 @@ hipError_t run_adjoint_step(const Plan &p, const Step &st, const void *in, void 
     }
     case Step::AdjGather: {
       const AdjPass &ps = p.adj.passes[st.index];
+      if (ps.block) {
+        return for_each_launch(p, rb, st, true, ps.tile, batch, [&](auto r, unsigned gy, unsigned gz, const RaggedMap &rg) {
+          AdjBlockLaunch g{dim3(static_cast<unsigned>(ps.nblocks), gy, gz), stream, rg, decltype(r)::value, ps.to_input, &ps,
+                           p.dev_adj_leaves1 + ps.leaf_offset, p.dev_adj_places + ps.leaf_offset,
+                           p.dev_adj_mids + ps.mid_offset, p.dev_adj_outs + ps.out_offset,
+                           p.dev_adj_leaves2 + ps.leaf2_offset, p.dev_adj_heads + ps.head_offset,
+                           static_cast<int32_t>(nt), src.stride, src.bstride, dst.stride, dst.bstride};
+          return launch_adjoint_block<Tacc>(g, static_cast<const Tacc *>(src.ptr), static_cast<Tacc *>(dst.ptr));
+        }, ps.extra);
+      }
       if (ps.depth < 1 || ps.depth > 5) return hipErrorInvalidValue;
       const int rpw = adjoint_rows(p, st.index);
       const int cv = p.gather_vecs;
@@ -1029,6 +1040,12 @@ hipError_t set_staged_lds(int lds) {
 }
 
 hipError_t prepare_kernels(const Plan &p) {
+  for (const AdjPass &ps : p.adj.passes)
+    if (ps.block && adjoint_block_lds_bytes(ps) > 64 * 1024) {
+      const hipError_t e = prepare_adjoint_blocks();
+      if (e != hipSuccess) return e;
+      break;
+    }
   size_t lds = 0;
   for (const Pass &ps : p.fwd.passes)
     if (!ps.gather && ps.kind != PassKind::Block) lds = std::max(lds, fused_lds_bytes(ps));
@@ -1187,6 +1204,7 @@ int step_tile(const Plan &p, bool adjoint, int i) {
     case Step::MergeAdj:
     case Step::InitAdj: return kTile;
     case Step::AdjGather:
+      if (p.adj.passes[st.index].block) return p.adj.passes[st.index].tile;
       return adjoint_wave_span(p.gather_vecs, p.adj.passes[st.index].lagged) *
              (adjoint_threads(p, st.index) / 64 / adjoint_rows(p, st.index));
     case Step::Fused: {
@@ -1198,6 +1216,12 @@ int step_tile(const Plan &p, bool adjoint, int i) {
     }
   }
   return 0;
+}
+
+int32_t step_extra(const Plan &p, bool adjoint, int i) {
+  if (!adjoint) return 0;
+  const Step &st = p.adj_steps[i];
+  return st.kind == Step::AdjGather && p.adj.passes[st.index].block ? p.adj.passes[st.index].extra : 0;
 }
 
 } // namespace fdmt

@@ -92,6 +92,23 @@ size_t block_lds_bytes(const Pass &ps);
 template <typename Tsrc, typename Tacc, typename Tdst, bool FROM_INPUT>
 hipError_t launch_block(const BlockLaunch &g, const Tsrc *src, Tdst *dst);
 
+// One launch of an adjoint block pass (see AdjBlockOut).
+struct AdjBlockLaunch {
+  dim3 grid;  // blocks, time tiles, beams
+  hipStream_t stream;
+  RaggedMap rg;
+  bool ragged, streaming;
+  const AdjPass *pass;
+  const void *leaves1, *places1, *mids, *outs, *leaves2, *heads;  // the pass's records on the device
+  int32_t nt;
+  int64_t src_stride, src_bstride, dst_stride, dst_bstride;
+};
+size_t adjoint_block_lds_bytes(const AdjPass &ps);
+// Sets the dynamic-LDS limit of the adjoint block kernels (windows of 512 samples need more than 64 KiB).
+hipError_t prepare_adjoint_blocks();
+template <typename Tacc>
+hipError_t launch_adjoint_block(const AdjBlockLaunch &g, const Tacc *src, Tacc *dst);
+
 // Adjoint register gather over a depth-first leaf list; max_shift bounds the
 // shifts of every leaf.
 template <typename Tacc>

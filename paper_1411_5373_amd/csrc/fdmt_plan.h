@@ -83,6 +83,10 @@ struct Plan {
   // -shift of its row, low and high word, then the chain of an input term.
   std::vector<InTerm> block_iplaces;
   std::vector<Term> block_places;
+  std::vector<AdjBlockLeaf> adj_places;  // the same of the adjoint's stage-1 leaves, branch depth in the low two bits
+  const AdjBlockLeaf *dev_adj_leaves1 = nullptr, *dev_adj_places = nullptr;
+  const int32_t *dev_adj_mids = nullptr, *dev_adj_leaves2 = nullptr, *dev_adj_heads = nullptr;
+  const AdjBlockOut *dev_adj_outs = nullptr;
   const int4 *dev_block_iplaces = nullptr;
   const int2 *dev_block_places = nullptr;
   const int32_t *dev_block_offs = nullptr;
@@ -105,10 +109,11 @@ struct RaggedBatch {
   const int4 *beam = nullptr;       // per beam {nt, padded nt, first sample, first padded sample}
   struct Map {
     int tile;            // time-tile width
+    int32_t extra;       // samples past each beam's end that its tiles cover too
     int64_t count;       // tiles over all beams
     const int2 *tiles;   // per tile {beam, tile index within the beam}
   };
-  std::vector<Map> maps;            // one per tile width the plan's steps use
+  std::vector<Map> maps;            // one per tile width and extra the plan's steps use
 };
 
 // Builds fwd_steps/adj_steps and ws_rows from the tables and the schedule.
@@ -131,6 +136,8 @@ hipError_t launch_forward_search(const Plan &p, const void *in, float *out, int 
                                  int max_log2, hipStream_t stream);
 // Time-tile width of a step's launches; 0 when the step has no ragged form.
 int step_tile(const Plan &p, bool adjoint, int step);
+// Samples past a record's end that a step's tiles cover (adjoint block passes).
+int32_t step_extra(const Plan &p, bool adjoint, int step);
 // Output rows per workgroup of adjoint register-gather pass `pass`.
 int adjoint_rows(const Plan &p, int pass);
 // Output rows and workgroup size of forward register-gather pass `ps`.

@@ -11,6 +11,7 @@
 #include "fdmt_schedule.h"
 
 #include <algorithm>
+#include <array>
 
 namespace fdmt {
 
@@ -557,6 +558,16 @@ std::string build_schedule(Schedule &s, const Tables &t, const ScheduleParams &p
 
 namespace {
 
+// Ranges of at most `most` rows that a sub-band's n rows are split into, one of
+// `subs` sub-bands: with few sub-bands as many as make the blocks a multiple of
+// the 8 XCDs, so that a range of blocks stays on its XCD from one time tile to
+// the next (57 blocks instead of 64 made a pass 12% slower).
+int row_parts(int n, int most, int subs) {
+  const int parts = (n + most - 1) / most;
+  const int step = subs >= 8 ? 1 : 8 / subs;
+  return parts < step ? parts : (parts + step - 1) / step * step;
+}
+
 // How a block pass of k iterations splits over its stages: two iterations
 // loaded through the caches, at most three from LDS at a time.
 struct BlockSplit {
@@ -635,7 +646,7 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
   const int64_t tiles = (nt + kBlockPitch - 33) / (kBlockPitch - 32);
   const auto count_blocks = [&]() {
     int64_t n = 0;
-    for (int32_t r : t.rows[ps.l1]) n += (r + max_rows - 1) / max_rows;
+    for (int32_t r : t.rows[ps.l1]) n += row_parts(r, max_rows, t.slots >> ps.l1);
     return n;
   };
   while (max_rows > 4 && count_blocks() * tiles < 256) max_rows /= 2;
@@ -648,7 +659,7 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
   int spread = 0;
   for (int sub = 0; sub < (t.slots >> ps.l1); ++sub) {
     const int n = t.rows[ps.l1][sub];
-    const int nb = (n + max_rows - 1) / max_rows;
+    const int nb = row_parts(n, max_rows, t.slots >> ps.l1);
     for (int b = 0; b < nb; ++b) {
       const int r0 = static_cast<int>(static_cast<int64_t>(n) * b / nb);
       const int r1 = static_cast<int>(static_cast<int64_t>(n) * (b + 1) / nb);
@@ -887,6 +898,202 @@ std::string build_adjoint_schedule(AdjSchedule &s, const Tables &t, int levels_p
     }
     s.passes.push_back(ps);
     l_hi = ps.l_lo;
+  }
+  return "";
+}
+
+namespace {
+
+// One output row of a block pass: its leaves in plane m (row, shift, branch).
+struct AdjOutRow {
+  int32_t row, sub;  // plane l_lo row (or channel) and its sub-band
+  std::vector<AdjLeaf> leaves;
+};
+
+std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt, int l_hi, int l_lo, bool to_input) {
+  AdjPass ps;
+  ps.block = true;
+  ps.l_hi = l_hi;
+  ps.l_lo = l_lo;
+  ps.to_input = to_input;
+  const int k = l_hi - l_lo;
+  ps.k1 = k >= 3 ? 2 : 1;
+  const int m = l_hi - ps.k1;
+  ps.depth2 = k - ps.k1 + (to_input ? 1 : 0);
+  ps.depth = k + (to_input ? 1 : 0);
+  ps.nrows = static_cast<int>(to_input ? t.nf : t.total[l_lo]);
+  ps.head_offset = static_cast<int64_t>(s.block_heads.size());
+  ps.mid_offset = static_cast<int64_t>(s.block_mids.size());
+  ps.out_offset = static_cast<int64_t>(s.block_outs.size());
+  ps.leaf_offset = static_cast<int64_t>(s.block_leaves1.size());
+  ps.leaf2_offset = static_cast<int64_t>(s.block_leaves2.size());
+  // Output rows of every sub-band of plane m with channels, by their first row.
+  const int subs = (t.nf + (1 << m) - 1) >> m;
+  std::vector<std::vector<AdjOutRow>> outs(subs);
+  int64_t rows = 0;
+  for (int x = 0; x < subs; ++x) {
+    rows += t.rows[m][x];
+    for (int q = x << (m - l_lo); q < (x + 1) << (m - l_lo) && (static_cast<int64_t>(q) << l_lo) < t.nf; ++q) {
+      const int n = to_input ? 1 : t.rows[l_lo][q];
+      for (int r = 0; r < n; ++r) {
+        AdjOutRow o{to_input ? q : static_cast<int32_t>(t.row_off[l_lo][q] + r), q, {}};
+        AdjWalker w{t, m, o.leaves};
+        if (to_input) {
+          for (int d = 0; d < t.leaf_rows[q]; ++d)
+            for (int i = 0; i <= d; ++i) w.visit(0, t.leaf_off[q] + d, t.pre[q] + i, 1, 0);
+        } else {
+          w.visit(l_lo, o.row, 0, 0, 0);
+        }
+        if (o.leaves.empty()) return "output row without leaves";
+        outs[x].push_back(std::move(o));
+      }
+    }
+    std::stable_sort(outs[x].begin(), outs[x].end(),
+                     [](const AdjOutRow &a, const AdjOutRow &b) { return a.leaves.front().row < b.leaves.front().row; });
+  }
+  // Windows of 512 samples, outputs on whole 128-byte lines, where that leaves
+  // each CU's two workgroups of 1024 threads more than once their work (Nf=4096,
+  // Nt=65536, Nd=2048: 1.05 ms against 1.20 ms with windows of 256); below, twice
+  // the workgroups of half the size (Nf=Nd=1024, Nt=8192: 75 us against 86 us).
+  int own = 28;
+  const auto workgroups = [&](int pitch) { return (rows + own - 1) / own * ((nt + pitch - 33) / (pitch - 32)); };
+  ps.pitch = workgroups(512) >= 1024 ? 512 : 256;
+  const int align = ps.pitch == 512 ? 32 : 4;
+  // Fewer rows of plane m per range where the blocks would leave CUs idle; a
+  // sub-band of no more than `most` rows stays whole: no row is then made twice.
+  int most = kAdjBlockRows;
+  while (own > 7 && workgroups(ps.pitch) < 256) most = own /= 2;
+  // Ranges, gathered into blocks while their rows fit LDS.
+  struct Piece {
+    int x, first, last;  // outs[x][first .. last - 1]
+    int32_t lo, hi;      // rows lo .. hi of plane m
+  };
+  std::vector<Piece> block;
+  typedef std::array<int32_t, kAdjBlockHeader> Head;
+  std::vector<Head> heads;
+  int block_rows = 0, spread = 0;
+  std::vector<AdjLeaf> leaves;
+  const auto flush = [&]() {
+    if (block.empty()) return;
+    int32_t head[kAdjBlockHeader] = {};
+    head[0] = static_cast<int32_t>(s.block_mids.size() - ps.mid_offset);
+    head[2] = static_cast<int32_t>(s.block_outs.size() - ps.out_offset);
+    int base = 0;
+    for (const Piece &p : block) {
+      // The range's smallest stage-1 shift moves its window instead of its
+      // leaves: every range then reads plane l_hi over one and the same time.
+      int32_t lag = INT32_MAX;
+      const size_t first = s.block_leaves1.size();
+      for (int32_t r = p.lo; r <= p.hi; ++r) {
+        leaves.clear();
+        AdjWalker w{t, l_hi, leaves};
+        w.visit(m, r, 0, 0, 0);
+        s.block_mids.push_back(static_cast<int32_t>(s.block_leaves1.size() - ps.leaf_offset));
+        for (const AdjLeaf &e : leaves) {
+          s.block_leaves1.push_back(AdjBlockLeaf{e.row, 4 * e.shift + e.branch});
+          lag = std::min(lag, e.shift);
+        }
+      }
+      for (size_t j = first; j < s.block_leaves1.size(); ++j) {
+        s.block_leaves1[j].shift4 -= 4 * lag;
+        head[4] = std::max(head[4], s.block_leaves1[j].shift4 >> 2);
+      }
+      // each output sub-band's smallest shift in this range is its offset
+      for (int i = p.first; i < p.last;) {
+        // rows of one sub-band need not be consecutive: offsets by sub-band
+        int32_t beta = INT32_MAX;
+        const int sub = outs[p.x][i].sub;
+        for (int j = p.first; j < p.last; ++j)
+          if (outs[p.x][j].sub == sub)
+            for (const AdjLeaf &e : outs[p.x][j].leaves) beta = std::min(beta, e.shift);
+        beta -= (beta + lag) & (align - 1);
+        const AdjOutRow &o = outs[p.x][i];
+        AdjBlockOut b{static_cast<int32_t>(s.block_leaves2.size() - ps.leaf2_offset), 0, o.row, beta + lag};
+        for (const AdjLeaf &e : o.leaves) {
+          s.block_leaves2.push_back(((base + e.row - p.lo) * ps.pitch + e.shift - beta) * 4 + e.branch);
+          spread = std::max(spread, e.shift - beta);
+        }
+        b.last = static_cast<int32_t>(s.block_leaves2.size() - ps.leaf2_offset);
+        s.block_outs.push_back(b);
+        head[5] = std::max(head[5], beta + lag);
+        ++i;
+      }
+      base += p.hi - p.lo + 1;
+    }
+    head[1] = static_cast<int32_t>(s.block_mids.size() - ps.mid_offset) - head[0];
+    head[3] = static_cast<int32_t>(s.block_outs.size() - ps.out_offset) - head[2];
+    head[6] = s.block_leaves1[ps.leaf_offset + s.block_mids[ps.mid_offset + head[0]]].row;
+    heads.push_back(Head{});
+    std::copy(head, head + kAdjBlockHeader, heads.back().begin());
+    ps.rows_mid = std::max(ps.rows_mid, base);
+    ps.extra = std::max(ps.extra, head[5]);
+    ++ps.nblocks;
+    block.clear();
+    block_rows = 0;
+  };
+  for (int x = 0; x < subs; ++x) {
+    const int n = t.rows[m][x];
+    const int32_t off = static_cast<int32_t>(t.row_off[m][x]);
+    const int parts = n <= most ? 1 : row_parts(n, own, subs);
+    size_t i = 0;
+    for (int b = 0; b < parts; ++b) {
+      const int32_t end = off + static_cast<int32_t>(static_cast<int64_t>(n) * (b + 1) / parts);
+      Piece p{x, static_cast<int>(i), 0, INT32_MAX, -1};
+      for (; i < outs[x].size() && outs[x][i].leaves.front().row < end; ++i)
+        for (const AdjLeaf &e : outs[x][i].leaves) {
+          p.lo = std::min(p.lo, e.row);
+          p.hi = std::max(p.hi, e.row);
+        }
+      p.last = static_cast<int>(i);
+      if (p.first == p.last) continue;
+      const int have = p.hi - p.lo + 1;
+      if (have > kAdjBlockRows) return "block rows do not fit LDS";
+      if (block_rows + have > kAdjBlockRows || block_rows >= own) flush();
+      block.push_back(p);
+      block_rows += have;
+    }
+  }
+  flush();
+  s.block_mids.push_back(static_cast<int32_t>(s.block_leaves1.size() - ps.leaf_offset));
+  // blocks of several sub-bands read the same rows of plane l_hi: run them next
+  // to each other, on one XCD
+  std::stable_sort(heads.begin(), heads.end(), [](const Head &a, const Head &b) { return a[6] < b[6]; });
+  for (const Head &h : heads) s.block_heads.insert(s.block_heads.end(), h.begin(), h.end());
+  ps.leaf1_count = static_cast<int64_t>(s.block_leaves1.size()) - ps.leaf_offset;
+  ps.leaves = ps.leaf1_count;
+  ps.tile = (ps.pitch - spread) / align * align;
+  if (ps.tile < 128 || spread > 128) return "block shifts spread too far";
+  if (s.block_leaves1.size() > static_cast<size_t>(INT32_MAX) || s.block_leaves2.size() > static_cast<size_t>(INT32_MAX))
+    return "adjoint schedule too large";
+  for (int64_t x = ps.leaf_offset; x < ps.leaf_offset + ps.leaf1_count; ++x) {
+    const AdjBlockLeaf &e = s.block_leaves1[x];
+    if (e.row < 0 || e.row >= t.total[l_hi] || e.shift4 < 0 || (e.shift4 & 3) >= ps.k1) return "adjoint leaf out of range";
+  }
+  for (size_t x = ps.leaf2_offset; x < s.block_leaves2.size(); ++x) {
+    const int32_t e = s.block_leaves2[x];
+    if (e < 0 || (e & 3) >= ps.depth2 || e / 4 / ps.pitch >= ps.rows_mid) return "adjoint LDS leaf out of range";
+  }
+  s.passes.push_back(ps);
+  return "";
+}
+
+} // namespace
+
+std::string build_adjoint_block_schedule(AdjSchedule &s, const Tables &t, int64_t nt) {
+  s = AdjSchedule();
+  const int L = t.levels;
+  if (L < 2) return "fewer than two iterations";
+  int fan = 0;
+  for (int k = 0; k < t.nf; ++k) fan = std::max(fan, t.leaf_rows[k] * (t.leaf_rows[k] + 1) / 2);
+  s.init_separate = fan > 16;
+  const int passes = (L + 3) / 4;
+  int l_hi = L;
+  for (int i = 0; i < passes; ++i) {
+    const int k = (l_hi + passes - i - 1) / (passes - i);
+    const std::string err =
+        build_adjoint_block_pass(s, t, nt, l_hi, l_hi - k, i == passes - 1 && !s.init_separate);
+    if (!err.empty()) return err;
+    l_hi -= k;
   }
   return "";
 }

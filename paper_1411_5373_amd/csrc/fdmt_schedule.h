@@ -203,6 +203,47 @@ struct AdjPass {
   int64_t leaves = 0;         // leaves of this pass
   int32_t max_shift = 0;      // largest leaf shift of this pass
   bool lagged = false;        // subtrees listed once with their lag count (see AdjLeaf)
+  // Block pass (see AdjBlockOut): iterations of its first stage, tree depth of
+  // its second, samples per window and tile, blocks, most LDS rows of a block, largest
+  // time offset of an output, and where its records start.
+  bool block = false;
+  int k1 = 0, depth2 = 0, pitch = 0, tile = 0, nblocks = 0, rows_mid = 0;
+  int32_t extra = 0;
+  int64_t head_offset = 0, mid_offset = 0, out_offset = 0, leaf1_count = 0, leaf2_offset = 0;
+};
+
+// Block passes of the adjoint. Between the planes l_hi and l_lo lies plane m =
+// l_hi - k1. A work item is a set of row ranges of sub-bands of plane m over
+// one window of time [T0, T0 + pitch), with the output rows whose first
+// row of plane m it owns:
+//   stage 1: each row of its ranges, the nested sum of its leaves in plane
+//            l_hi, into LDS;
+//   stage 2: each output row, the nested sum of its rows of plane m in LDS.
+// The window is one of plane l_hi: a range whose leaves have shifts lag, lag + 1,
+// ... holds plane m from T0 - lag on, and an output row reading that at shifts
+// beta0, beta0 + 1, ... gets its samples from T0 - beta on, beta = lag + beta0.
+// Each output row is tiled with an offset of its own, and `extra` (the largest
+// beta) more samples of windows cover every row's end. Sub-bands at large
+// shifts thus read the samples their neighbours read at the same time (with a
+// common window of plane m a pass fetched each 2.7 times). Sub-bands without
+// channels have no rows here: nothing reads them.
+//
+// Per block: [0] first row of plane m (in block_mids), [1] their number, [2]
+// first output (in block_outs), [3] their number, [4] largest shift of its
+// stage-1 leaves, [5] largest beta, [6] its first row of plane l_hi (the order
+// of the blocks).
+constexpr int kAdjBlockHeader = 8;
+constexpr int kAdjBlockRows = 36;  // most LDS rows of a block (72 KiB of windows of 512 samples, two workgroups per CU)
+
+// Output row `row`: its leaves are [first, last) of block_leaves2, LDS byte
+// offsets of its first sample with the branch depth (see AdjLeaf) in the low
+// two bits. A stage-1 leaf (AdjBlockLeaf) is a row of plane l_hi and 4 * shift
+// + branch depth.
+struct AdjBlockOut {
+  int32_t first, last, row, beta;
+};
+struct AdjBlockLeaf {
+  int32_t row, shift4;
 };
 
 struct AdjSchedule {
@@ -212,6 +253,11 @@ struct AdjSchedule {
   std::vector<int32_t> starts;  // per pass: leaf index (pass-relative) of each row, then the end
   std::vector<int32_t> order;   // per pass: output row of each position (rows that share
                                 // leaves are neighbours, so they meet in one XCD's L2)
+  std::vector<int32_t> block_heads;  // block passes: kAdjBlockHeader per block
+  std::vector<int32_t> block_mids;   // ... first stage-1 leaf (pass-relative) of each LDS row, then the end
+  std::vector<AdjBlockLeaf> block_leaves1;
+  std::vector<AdjBlockOut> block_outs;
+  std::vector<int32_t> block_leaves2;
 };
 
 // Largest lag count of a lagged pass: a channel's partial-sum rows are then
@@ -224,5 +270,9 @@ constexpr int kMaxLags = 4;
 // is lagged.
 std::string build_adjoint_schedule(AdjSchedule &s, const Tables &t, int levels_per_pass, int last_levels,
                                    bool lag_reuse = true);
+
+// The adjoint schedule of block passes for records of nt samples. Returns ""
+// on success, else why the tables do not suit it.
+std::string build_adjoint_block_schedule(AdjSchedule &s, const Tables &t, int64_t nt);
 
 } // namespace fdmt

@@ -45,3 +45,25 @@ def test_lengths_past_the_block_tiles_are_still_accepted():
     s = _plan(64, 2 * ok, 64, gather_vecs=2).steps()
     assert s[0]["kind"] == KINDS[2]
     assert _plan(4, 5000, 30).steps()[0]["kind"] == KINDS[2]  # fewer than three iterations
+
+
+def test_adjoint_block_passes():
+    for nf, passes in ((16, 1), (64, 2), (1024, 3), (4096, 3), (8192, 4)):
+        s = _plan(nf, 5000, min(nf, 64)).steps(True)
+        assert len(s) == passes and all(x["kind"] == KINDS[8] and x["lds_bytes"] > 0 for x in s)
+        assert s[0]["level_last"] == nf.bit_length() - 1 and s[-1]["level_first"] == 0
+    # long chains keep the transposed initialisation on its own
+    assert _plan(32, 5000, 2000).steps(True)[-1]["kind"] == KINDS[4]
+    for kw in (dict(adjoint_levels=2), dict(adjoint_last_levels=2), dict(gather_rows=8), dict(gather_vecs=2),
+               dict(adjoint_rows=4), dict(adjoint_threads=512), dict(adjoint_tile_major=1)):
+        assert all(x["lds_bytes"] == 0 for x in _plan(1024, 5000, 64, **kw).steps(True))
+    # past the block tiles, or with shifts that need too many more of them: the register gathers
+    assert all(x["lds_bytes"] == 0 for x in _plan(64, 65535 * 500, 64).steps(True))
+    assert all(x["lds_bytes"] == 0 for x in _plan(64, 5000, 64, d_min=1 << 30).steps(True))
+
+
+def test_adjoint_windows():
+    """Windows of 512 samples (more than 40 KB of LDS) once they fill the GPU."""
+    for nf, nt, nd, wide in ((256, 70001, 300, True), (2048, 20011, 1500, True), (1024, 8192, 1024, False),
+                             (128, 131072, 64, False)):
+        assert (_plan(nf, nt, nd).steps(True)[0]["lds_bytes"] > 40000) == wide
