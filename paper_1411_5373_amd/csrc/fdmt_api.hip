@@ -58,9 +58,14 @@ fdmt_status_t upload(fdmt::Plan &p) {
     return off;
   };
   size_t off_merge[32] = {}, off_adj[32] = {};
+  // the per-iteration tables are read by the per-iteration kernels alone
+  const auto runs = [](const std::vector<fdmt::Step> &steps, fdmt::Step::Kind k) {
+    return std::any_of(steps.begin(), steps.end(), [k](const fdmt::Step &st) { return st.kind == k; });
+  };
+  const bool merges = runs(p.fwd_steps, fdmt::Step::Merge), adj_merges = runs(p.adj_steps, fdmt::Step::MergeAdj);
   for (int l = 1; l <= T.levels; ++l) {
-    off_merge[l] = reserve(T.merge[l].size() * sizeof(fdmt::MergeRow));
-    off_adj[l] = reserve(T.adj[l].size() * sizeof(fdmt::AdjRow));
+    if (merges || adj_merges) off_merge[l] = reserve(T.merge[l].size() * sizeof(fdmt::MergeRow));
+    if (adj_merges) off_adj[l] = reserve(T.adj[l].size() * sizeof(fdmt::AdjRow));
   }
   const size_t off_leaf_off = reserve(T.leaf_off.size() * sizeof(int32_t));
   const size_t off_leaf_rows = reserve(T.leaf_rows.size() * sizeof(int32_t));
@@ -89,8 +94,9 @@ fdmt_status_t upload(fdmt::Plan &p) {
 
   std::vector<unsigned char> host(bytes, 0);
   for (int l = 1; l <= T.levels; ++l) {
-    std::memcpy(host.data() + off_merge[l], T.merge[l].data(), T.merge[l].size() * sizeof(fdmt::MergeRow));
-    std::memcpy(host.data() + off_adj[l], T.adj[l].data(), T.adj[l].size() * sizeof(fdmt::AdjRow));
+    if (merges || adj_merges)
+      std::memcpy(host.data() + off_merge[l], T.merge[l].data(), T.merge[l].size() * sizeof(fdmt::MergeRow));
+    if (adj_merges) std::memcpy(host.data() + off_adj[l], T.adj[l].data(), T.adj[l].size() * sizeof(fdmt::AdjRow));
   }
   std::memcpy(host.data() + off_leaf_off, T.leaf_off.data(), T.leaf_off.size() * sizeof(int32_t));
   std::memcpy(host.data() + off_leaf_rows, T.leaf_rows.data(), T.leaf_rows.size() * sizeof(int32_t));
@@ -143,8 +149,8 @@ fdmt_status_t upload(fdmt::Plan &p) {
   if (e != hipSuccess) return device_fail(e, "hipMemcpy of delay tables");
   auto *base = static_cast<unsigned char *>(p.dbuf);
   for (int l = 1; l <= T.levels; ++l) {
-    p.dev.merge[l] = reinterpret_cast<const int4 *>(base + off_merge[l]);
-    p.dev.adj[l] = reinterpret_cast<const int4 *>(base + off_adj[l]);
+    if (merges || adj_merges) p.dev.merge[l] = reinterpret_cast<const int4 *>(base + off_merge[l]);
+    if (adj_merges) p.dev.adj[l] = reinterpret_cast<const int4 *>(base + off_adj[l]);
   }
   p.dev.leaf_off = reinterpret_cast<const int32_t *>(base + off_leaf_off);
   p.dev.leaf_rows = reinterpret_cast<const int32_t *>(base + off_leaf_rows);

@@ -582,32 +582,31 @@ BlockSplit block_split(int k) {
   }
 }
 
-// The 2^k terms of row `row` of plane l, k iterations down, in the order the
-// recursion adds them.
-void walk_terms(const Tables &t, int l, int k, int64_t row, std::vector<Term> &cur, std::vector<Term> &tmp) {
-  cur.assign(1, Term{static_cast<int32_t>(row), 0});
-  for (int i = 0; i < k; ++i, --l) {
-    tmp.clear();
-    for (const Term &x : cur) {
+// The 2^k terms (k <= 3) of row `row` of plane l, k iterations down, in the
+// order the recursion adds them.
+void walk_terms(const Tables &t, int l, int k, int64_t row, Term (&out)[8]) {
+  out[0] = Term{static_cast<int32_t>(row), 0};
+  for (int i = 0; i < k; ++i, --l)
+    for (int j = (1 << i) - 1; j >= 0; --j) {
+      const Term x = out[j];
       const MergeRow &m = t.merge[l][x.row];
-      tmp.push_back(Term{m.lo, x.shift});
-      tmp.push_back(Term{m.hi, x.shift + m.s});
+      out[2 * j] = Term{m.lo, x.shift};
+      out[2 * j + 1] = Term{m.hi, x.shift + m.s};
     }
-    cur.swap(tmp);
-  }
 }
 
 // LDS offsets of the rows of `tops` (nodes k levels above `leaves`, which lie
 // in LDS from row base[i] on): appended to offs, in row order.
 std::string block_offsets(const Tables &t, int l, int k, const Node *tops, int ntops, const Node *leaves,
                           const std::vector<int> &base, int lead, int tile, std::vector<int32_t> &offs) {
-  std::vector<Term> cur, tmp;
+  Term cur[8];
+  const int terms = 1 << k;
   for (int j = 0; j < ntops; ++j) {
     const Node &n = tops[j];
     for (int r = 0; r < n.nrows; ++r) {
-      walk_terms(t, l, k, n.row0 + r, cur, tmp);
-      for (size_t q = 0; q < cur.size(); ++q) {
-        const size_t i = static_cast<size_t>(j) * cur.size() + q;
+      walk_terms(t, l, k, n.row0 + r, cur);
+      for (int q = 0; q < terms; ++q) {
+        const int i = j * terms + q;
         const Node &x = leaves[i];
         const int rl = cur[q].row - x.row0;
         if (rl < 0 || rl >= x.nrows) return "block term row outside its node";
@@ -656,7 +655,9 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
     Tree tree;
   };
   std::vector<Range> blocks;
+  blocks.reserve(count_blocks());
   int spread = 0;
+  size_t lds_rows = 0;
   for (int sub = 0; sub < (t.slots >> ps.l1); ++sub) {
     const int n = t.rows[ps.l1][sub];
     const int nb = row_parts(n, max_rows, t.slots >> ps.l1);
@@ -666,15 +667,20 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
       blocks.push_back({sub, r0, r1 - r0, build_tree(t, false, l0, ps.l1, sub, r0, r1 - r0, 0)});
       const Tree &tr = blocks.back().tree;
       // nodes level by level, leaves first: the nodes of level i start at 2^(k+1) - 2^(k+1-i)
-      for (size_t j = (2u << k) - (2u << (k - ps.k1)); j < tr.nodes.size(); ++j) spread = std::max(spread, tr.nodes[j].width);
+      const size_t a = (2u << k) - (2u << (k - ps.k1));
+      for (size_t j = a; j < tr.nodes.size(); ++j) spread = std::max(spread, tr.nodes[j].width);
+      for (size_t j = a; j < a + (1u << (k - ps.k1)); ++j) lds_rows += tr.nodes[j].nrows;
     }
   }
   const int lead = from_input ? kBlockLead : 0;
   ps.tile = (kBlockPitch - kBlockTail - spread - lead) / 32 * 32;
   if (ps.tile < 128) return "block shifts spread too far";
   if (from_input && static_cast<int64_t>(blocks.size()) * ((nt + ps.tile - 1) / ps.tile) >= 4096) ps.tiles_per_wg = 2;
-  std::vector<Term> cur, tmp;
+  Term cur[8];
+  const int terms1 = 1 << ps.k1;
   std::vector<int> base_a, base_b;
+  if (from_input) s.iterms.reserve(s.iterms.size() + lds_rows * terms1);
+  else s.terms.reserve(s.terms.size() + lds_rows * terms1);
   for (const Range &b : blocks) {
     const auto level = [&](int i) { return b.tree.nodes.data() + ((2 << k) - (2 << (k - i))); };
     const auto bases = [](const Node *n, int count, std::vector<int> &base) {
@@ -695,8 +701,9 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
     int reach = 0;
     for (int j = 0; j < count_a; ++j) {
       for (int r = 0; r < na[j].nrows; ++r) {
-        walk_terms(t, l0 + ps.k1, ps.k1, na[j].row0 + r, cur, tmp);
-        for (const Term &x : cur) {
+        walk_terms(t, l0 + ps.k1, ps.k1, na[j].row0 + r, cur);
+        for (int q = 0; q < terms1; ++q) {
+          const Term &x = cur[q];
           if (x.row < 0 || x.row >= t.total[l0] || x.shift < 0) return "block term out of range";
           const int shift = x.shift + na[j].win + lead;
           if (from_input) {
@@ -904,10 +911,11 @@ std::string build_adjoint_schedule(AdjSchedule &s, const Tables &t, int levels_p
 
 namespace {
 
-// One output row of a block pass: its leaves in plane m (row, shift, branch).
+// One output row of a block pass.
 struct AdjOutRow {
-  int32_t row, sub;  // plane l_lo row (or channel) and its sub-band
-  std::vector<AdjLeaf> leaves;
+  int32_t row, sub;     // plane l_lo row (or channel) and its sub-band
+  int32_t first, last;  // its leaves in plane m (row, shift, branch): [first, last) of a common list
+  int32_t lead;         // plane m row of the first leaf, its smallest
 };
 
 std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt, int l_hi, int l_lo, bool to_input) {
@@ -929,27 +937,34 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
   ps.leaf2_offset = static_cast<int64_t>(s.block_leaves2.size());
   // Output rows of every sub-band of plane m with channels, by their first row.
   const int subs = (t.nf + (1 << m) - 1) >> m;
-  std::vector<std::vector<AdjOutRow>> outs(subs);
+  std::vector<AdjOutRow> outs;
+  std::vector<size_t> out_of(subs + 1, 0);  // first output of each sub-band of plane m
+  std::vector<AdjLeaf> pool;
+  outs.reserve(ps.nrows);
+  pool.reserve(static_cast<size_t>(ps.nrows) * 5);
   int64_t rows = 0;
   for (int x = 0; x < subs; ++x) {
     rows += t.rows[m][x];
     for (int q = x << (m - l_lo); q < (x + 1) << (m - l_lo) && (static_cast<int64_t>(q) << l_lo) < t.nf; ++q) {
       const int n = to_input ? 1 : t.rows[l_lo][q];
       for (int r = 0; r < n; ++r) {
-        AdjOutRow o{to_input ? q : static_cast<int32_t>(t.row_off[l_lo][q] + r), q, {}};
-        AdjWalker w{t, m, o.leaves};
+        AdjOutRow o{to_input ? q : static_cast<int32_t>(t.row_off[l_lo][q] + r), q, static_cast<int32_t>(pool.size()), 0, 0};
+        AdjWalker w{t, m, pool};
         if (to_input) {
           for (int d = 0; d < t.leaf_rows[q]; ++d)
             for (int i = 0; i <= d; ++i) w.visit(0, t.leaf_off[q] + d, t.pre[q] + i, 1, 0);
         } else {
           w.visit(l_lo, o.row, 0, 0, 0);
         }
-        if (o.leaves.empty()) return "output row without leaves";
-        outs[x].push_back(std::move(o));
+        o.last = static_cast<int32_t>(pool.size());
+        if (o.first == o.last) return "output row without leaves";
+        o.lead = pool[o.first].row;
+        outs.push_back(o);
       }
     }
-    std::stable_sort(outs[x].begin(), outs[x].end(),
-                     [](const AdjOutRow &a, const AdjOutRow &b) { return a.leaves.front().row < b.leaves.front().row; });
+    out_of[x + 1] = outs.size();
+    std::stable_sort(outs.begin() + out_of[x], outs.end(),
+                     [](const AdjOutRow &a, const AdjOutRow &b) { return a.lead < b.lead; });
   }
   // Windows of 512 samples, outputs on whole 128-byte lines, where that leaves
   // each CU's two workgroups of 1024 threads more than once their work (Nf=4096,
@@ -965,7 +980,7 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
   while (own > 7 && workgroups(ps.pitch) < 256) most = own /= 2;
   // Ranges, gathered into blocks while their rows fit LDS.
   struct Piece {
-    int x, first, last;  // outs[x][first .. last - 1]
+    size_t first, last;  // outputs
     int32_t lo, hi;      // rows lo .. hi of plane m
   };
   std::vector<Piece> block;
@@ -973,6 +988,10 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
   std::vector<Head> heads;
   int block_rows = 0, spread = 0;
   std::vector<AdjLeaf> leaves;
+  std::vector<int32_t> betas;
+  s.block_leaves1.reserve(s.block_leaves1.size() + static_cast<size_t>(rows) * 6);
+  s.block_leaves2.reserve(s.block_leaves2.size() + pool.size());
+  s.block_outs.reserve(s.block_outs.size() + outs.size());
   const auto flush = [&]() {
     if (block.empty()) return;
     int32_t head[kAdjBlockHeader] = {};
@@ -998,25 +1017,27 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
         s.block_leaves1[j].shift4 -= 4 * lag;
         head[4] = std::max(head[4], s.block_leaves1[j].shift4 >> 2);
       }
-      // each output sub-band's smallest shift in this range is its offset
-      for (int i = p.first; i < p.last;) {
-        // rows of one sub-band need not be consecutive: offsets by sub-band
-        int32_t beta = INT32_MAX;
-        const int sub = outs[p.x][i].sub;
-        for (int j = p.first; j < p.last; ++j)
-          if (outs[p.x][j].sub == sub)
-            for (const AdjLeaf &e : outs[p.x][j].leaves) beta = std::min(beta, e.shift);
-        beta -= (beta + lag) & (align - 1);
-        const AdjOutRow &o = outs[p.x][i];
+      // each output sub-band's smallest shift in this range is its offset (the
+      // sub-bands under one of plane m are few and consecutive)
+      const int sub0 = (outs[p.first].sub >> (m - l_lo)) << (m - l_lo);
+      betas.assign(size_t(1) << (m - l_lo), INT32_MAX);
+      for (size_t i = p.first; i < p.last; ++i)
+        for (int32_t x = outs[i].first; x < outs[i].last; ++x)
+          betas[outs[i].sub - sub0] = std::min(betas[outs[i].sub - sub0], pool[x].shift);
+      for (int32_t &b : betas)
+        if (b != INT32_MAX) b -= (b + lag) & (align - 1);
+      for (size_t i = p.first; i < p.last; ++i) {
+        const AdjOutRow &o = outs[i];
+        const int32_t beta = betas[o.sub - sub0];
         AdjBlockOut b{static_cast<int32_t>(s.block_leaves2.size() - ps.leaf2_offset), 0, o.row, beta + lag};
-        for (const AdjLeaf &e : o.leaves) {
+        for (int32_t x = o.first; x < o.last; ++x) {
+          const AdjLeaf &e = pool[x];
           s.block_leaves2.push_back(((base + e.row - p.lo) * ps.pitch + e.shift - beta) * 4 + e.branch);
           spread = std::max(spread, e.shift - beta);
         }
         b.last = static_cast<int32_t>(s.block_leaves2.size() - ps.leaf2_offset);
         s.block_outs.push_back(b);
         head[5] = std::max(head[5], beta + lag);
-        ++i;
       }
       base += p.hi - p.lo + 1;
     }
@@ -1035,16 +1056,16 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
     const int n = t.rows[m][x];
     const int32_t off = static_cast<int32_t>(t.row_off[m][x]);
     const int parts = n <= most ? 1 : row_parts(n, own, subs);
-    size_t i = 0;
+    size_t i = out_of[x];
     for (int b = 0; b < parts; ++b) {
       const int32_t end = off + static_cast<int32_t>(static_cast<int64_t>(n) * (b + 1) / parts);
-      Piece p{x, static_cast<int>(i), 0, INT32_MAX, -1};
-      for (; i < outs[x].size() && outs[x][i].leaves.front().row < end; ++i)
-        for (const AdjLeaf &e : outs[x][i].leaves) {
-          p.lo = std::min(p.lo, e.row);
-          p.hi = std::max(p.hi, e.row);
+      Piece p{i, i, INT32_MAX, -1};
+      for (; i < out_of[x + 1] && outs[i].lead < end; ++i)
+        for (int32_t y = outs[i].first; y < outs[i].last; ++y) {
+          p.lo = std::min(p.lo, pool[y].row);
+          p.hi = std::max(p.hi, pool[y].row);
         }
-      p.last = static_cast<int>(i);
+      p.last = i;
       if (p.first == p.last) continue;
       const int have = p.hi - p.lo + 1;
       if (have > kAdjBlockRows) return "block rows do not fit LDS";
