@@ -351,7 +351,9 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
                       !o.first_kernel && !o.later_kernel && !o.stream_tiles && !o.gather_rows && !o.gather_threads &&
                       !o.first_rows && !o.first_threads;
     try {
-      bool block = open && fdmt::build_block_schedule(p.fwd, p.tab, nt, o.search_rows > 0).empty();
+      bool block = open && fdmt::build_block_schedule(p.fwd, p.tab, nt, o.search_rows > 0,
+                                                       o.in_dtype == FDMT_U8 && !(o.flags & FDMT_PLAN_WIDE_PLANES))
+                               .empty();
       for (const fdmt::Pass &ps : p.fwd.passes)
         if (block && ps.kind == fdmt::PassKind::Block && (nt + ps.tile - 1) / ps.tile > 65535) block = false;
       const std::string err = block ? "" : fdmt::build_schedule(p.fwd, p.tab, sp);

@@ -339,6 +339,188 @@ __global__ __launch_bounds__(kBlockThreads, 8) void block_pass_kernel(const Tsrc
   }
 }
 
+// The same for a first pass from uint8 input whose sums all stay below 2^16:
+// LDS holds two samples per word (no half carries into the other), a row is 512
+// samples, and one addition, LDS access and store serves two, for a kernel that
+// its instructions bound. A lane loads 8 samples. A stage-2 or -3 term at an odd
+// column takes each word's halves from two words, so five iterations go through
+// LDS twice (eight such terms at a time were 14% slower). Measured: the first
+// pass of Nf=4096, Nt=65536, Nd=2048 0.287 -> 0.219 ms, of four beams of Nf=128,
+// Nt=50000 40 -> 28 us, of Nf=1000, Nt=40001 55 -> 50 us.
+template <int K>
+__device__ __forceinline__ void packed_terms(uint32_t (&out)[4], const uint32_t *area, Const<int32_t> off, int lane) {
+  constexpr int N = 1 << K;
+  int o[N];
+  uint32_t v[N][4], w[N][4];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    o[j] = off[j];
+    const uint32_t *p = area + (o[j] >> 1) + lane;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[j][c] = p[64 * c];
+  }
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    if (o[j] & 1) {
+      const uint32_t *p = area + (o[j] >> 1) + 1 + lane;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) w[j][c] = p[64 * c];
+    }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) out[c] = 0;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    if (o[j] & 1) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[j][c] = __builtin_amdgcn_alignbyte(w[j][c], v[j][c], 2);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) out[c] += v[j][c];
+  }
+}
+
+template <typename Tdst, int K1, int K2, int K3, bool RAGGED>
+__global__ __launch_bounds__(kBlockThreads, 8) void packed_block_kernel(const uint8_t *__restrict__ src,
+                                                                     Tdst *__restrict__ dst, BlockArgs a,
+                                                                     RaggedMap rg) {
+  constexpr int N1 = 1 << K1;
+  constexpr int kPitch = 2 * kBlockPitch, kWords = kBlockPitch;  // samples and words per LDS row
+  typedef uint32_t Words2 __attribute__((ext_vector_type(2), aligned(4)));
+  typedef uint32_t Words4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  uint32_t *area_a = reinterpret_cast<uint32_t *>(lds_raw);
+  uint32_t *area_b = area_a + a.rows_a * kWords;
+  const int wave = uniform(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int block = xcd_local_order(blockIdx.x, a.nblocks);
+  BeamSpan bs = beam_span<RAGGED>(rg, a.nt, a.src_stride, a.src_bstride, a.dst_stride, a.dst_bstride);
+  if (!RAGGED && rg.reverse) bs.tile = static_cast<int>(gridDim.y) - 1 - bs.tile;
+  const int nt = bs.nt;
+  const Const<int32_t> head = as_const<int32_t>(a.heads) + static_cast<int64_t>(block) * kBlockHeader;
+  const Const<int32_t> offs = as_const<int32_t>(a.offs);
+  const uint8_t *base = src + bs.src_off;
+  const Const<Int4> terms = as_const<Int4>(a.terms) + head[0];
+  const Const<Int4> places = as_const<Int4>(a.places) + head[0];
+  // Adds a term's chain: w0 and w1 hold a lane's samples 0-3 and 4-7, the four
+  // before them are the neighbour lane's. even: samples 0, 2 and 4, 6; odd the
+  // others, one per half word.
+  const auto add_chain = [](uint32_t (&even)[2], uint32_t (&odd)[2], uint32_t w0, uint32_t w1, int chain) {
+    even[0] += w0 & 0x00ff00ffu;
+    odd[0] += (w0 >> 8) & 0x00ff00ffu;
+    even[1] += w1 & 0x00ff00ffu;
+    odd[1] += (w1 >> 8) & 0x00ff00ffu;
+    if (chain > 0) {
+      const uint32_t before = lane_before(w1);
+      for (int d = 1; d <= chain; ++d) {
+        const uint32_t y0 = d < 4 ? __builtin_amdgcn_alignbyte(w0, before, 4 - d) : before;
+        const uint32_t y1 = d < 4 ? __builtin_amdgcn_alignbyte(w1, w0, 4 - d) : w0;
+        even[0] += y0 & 0x00ff00ffu;
+        odd[0] += (y0 >> 8) & 0x00ff00ffu;
+        even[1] += y1 & 0x00ff00ffu;
+        odd[1] += (y1 >> 8) & 0x00ff00ffu;
+      }
+    }
+  };
+  const auto put_row = [&](int r, const uint32_t (&even)[2], const uint32_t (&odd)[2]) {
+    *reinterpret_cast<Words4 *>(area_a + r * kWords + 4 * lane) =
+        Words4{__builtin_amdgcn_perm(odd[0], even[0], 0x05040100u), __builtin_amdgcn_perm(odd[0], even[0], 0x07060302u),
+               __builtin_amdgcn_perm(odd[1], even[1], 0x05040100u), __builtin_amdgcn_perm(odd[1], even[1], 0x07060302u)};
+  };
+  // the aligned words may start 3 bytes before a term's samples: see block_pass_kernel
+  const int room = (reinterpret_cast<uintptr_t>(src) & 3) != 0 ? 4 : 0;
+  int t0 = bs.tile * a.tiles_per_wg * a.tile;
+  for (int tile = 0; tile < a.tiles_per_wg && t0 < nt; ++tile, t0 += a.tile) {
+    if (K2 == 0 && tile > 0) __syncthreads();
+    if (t0 - room >= head[7] && t0 + kPitch <= nt) {
+      row_batches<8 / N1>(wave, head[1], [&](int r, auto batch) {
+        constexpr int RU = decltype(batch)::value;
+        int mis[RU][N1], chain[RU][N1];
+        Words2 x[RU][N1];
+#pragma unroll
+        for (int u = 0; u < RU; ++u)
+#pragma unroll
+          for (int j = 0; j < N1; ++j) {
+            const int i = (r + u * kBlockWaves) * N1 + j;
+            const uint8_t *p;  // wave-uniform
+            if constexpr (RAGGED) {
+              const Int4 e = terms[i];
+              p = base + row_offset(e.x, bs.src_stride) + (t0 - e.y);
+              chain[u][j] = e.z;
+            } else {
+              const Int4 e = places[i];
+              const uint64_t at = static_cast<uint64_t>(static_cast<uint32_t>(e.y)) << 32 | static_cast<uint32_t>(e.x);
+              p = base + t0 + static_cast<int64_t>(at);
+              chain[u][j] = e.z;
+            }
+            mis[u][j] = static_cast<int>(reinterpret_cast<uintptr_t>(p) & 3);
+            x[u][j] = *reinterpret_cast<const Words2 *>(p - mis[u][j] + 8 * lane);
+          }
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+          uint32_t even[2] = {0, 0}, odd[2] = {0, 0};
+#pragma unroll
+          for (int j = 0; j < N1; ++j) {
+            const uint32_t m = static_cast<uint32_t>(mis[u][j]);
+            add_chain(even, odd, __builtin_amdgcn_alignbyte(x[u][j][1], x[u][j][0], m),
+                      __builtin_amdgcn_alignbyte(lane_after(x[u][j][0]), x[u][j][1], m), chain[u][j]);
+          }
+          put_row(r + u * kBlockWaves, even, odd);
+        }
+      });
+    } else {
+      for (int r = wave; r < head[1]; r += kBlockWaves) {
+        uint32_t even[2] = {0, 0}, odd[2] = {0, 0};
+        for (int j = 0; j < N1; ++j) {
+          const Int4 e = terms[r * N1 + j];
+          const uint8_t *p = base + row_offset(e.x, bs.src_stride);
+          const int ts = t0 - e.y + 8 * lane;
+          uint32_t w[2] = {0, 0};
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const int t = ts + i < 0 ? 0 : ts + i < nt ? ts + i : nt - 1;
+            const uint32_t z = p[t];
+            w[i / 4] |= (ts + i >= 0 ? z : 0u) << (8 * (i % 4));
+          }
+          add_chain(even, odd, w[0], w[1], e.z);
+        }
+        put_row(r, even, odd);
+      }
+    }
+    __syncthreads();
+    const uint32_t *last = area_a;
+    if constexpr (K2 > 0) {
+      for (int r = wave; r < head[3]; r += kBlockWaves) {
+        uint32_t v[4];
+        packed_terms<K2>(v, area_a, offs + head[2] + r * (1 << K2), lane);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) area_b[r * kWords + 64 * c + lane] = v[c];
+      }
+      __syncthreads();
+      last = area_b;
+    }
+    const int valid = nt - t0 < a.tile ? nt - t0 : a.tile;
+    for (int r = wave; r < head[5]; r += kBlockWaves) {
+      uint32_t v[4];
+      packed_terms<K3>(v, last, offs + head[4] + r * (1 << K3), lane);
+      Tdst *o = dst + bs.dst_off + (head[6] + r) * bs.dst_stride + t0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int col = 128 * c + 2 * lane;
+        if (col + 1 < valid) {
+          if constexpr (sizeof(Tdst) == 2) {
+            *reinterpret_cast<uint32_t *>(o + col) = v[c];  // plane rows and tiles start on words
+          } else {
+            typedef Tdst D2 __attribute__((ext_vector_type(2), aligned(4)));
+            const D2 d = {static_cast<Tdst>(v[c] & 0xffffu), static_cast<Tdst>(v[c] >> 16)};
+            __builtin_nontemporal_store(d, reinterpret_cast<D2 *>(o + col));
+          }
+        } else if (col < valid) {
+          o[col] = static_cast<Tdst>(v[c] & 0xffffu);
+        }
+      }
+    }
+  }
+}
+
 } // namespace
 
 size_t block_lds_bytes(const Pass &ps) {
@@ -366,6 +548,28 @@ hipError_t launch_block(const BlockLaunch &g, const Tsrc *src, Tdst *dst) {
   a.dst_bstride = g.dst_bstride;
   const size_t lds = block_lds_bytes(ps);
   if (lds > 64 * 1024) return hipErrorInvalidValue;
+  // uint8 input into integer sums that all fit 16 bits
+  constexpr bool kBytes = FROM_INPUT && std::is_same<Tsrc, uint8_t>::value && std::is_same<Tacc, int32_t>::value;
+  if (ps.packed) {
+    if constexpr (kBytes) {
+#define FDMT_PACKED(A, B, C)                                                                                       \
+  if (ps.k1 == A && ps.k2 == B && ps.k3 == C) {                                                                    \
+    if (g.ragged)                                                                                                  \
+      hipLaunchKernelGGL((packed_block_kernel<Tdst, A, B, C, true>), g.grid, dim3(kBlockThreads), lds, g.stream,   \
+                         src, dst, a, g.rg);                                                                       \
+    else                                                                                                           \
+      hipLaunchKernelGGL((packed_block_kernel<Tdst, A, B, C, false>), g.grid, dim3(kBlockThreads), lds, g.stream,  \
+                         src, dst, a, g.rg);                                                                       \
+    return hipGetLastError();                                                                                      \
+  }
+      FDMT_PACKED(1, 0, 2)
+      FDMT_PACKED(2, 0, 2)
+      FDMT_PACKED(2, 1, 2)
+      FDMT_PACKED(2, 2, 2)
+#undef FDMT_PACKED
+    }
+    return hipErrorInvalidValue;
+  }
 #define FDMT_BLOCK(A, B, C)                                                                                        \
   if (ps.k1 == A && ps.k2 == B && ps.k3 == C) {                                                                    \
     if (g.ragged)                                                                                                  \

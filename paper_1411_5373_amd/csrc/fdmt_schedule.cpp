@@ -569,15 +569,16 @@ int row_parts(int n, int most, int subs) {
 }
 
 // How a block pass of k iterations splits over its stages: two iterations
-// loaded through the caches, at most three from LDS at a time.
+// loaded through the caches, at most three from LDS at a time (five iterations
+// of 32-bit sums as 2 + 1 + 2 were 9% slower than as 2 + 3).
 struct BlockSplit {
   int k1, k2, k3;
 };
-BlockSplit block_split(int k) {
+BlockSplit block_split(int k, bool packed) {
   switch (k) {
     case 3: return {1, 0, 2};
     case 4: return {2, 0, 2};
-    case 5: return {2, 0, 3};
+    case 5: return packed ? BlockSplit{2, 1, 2} : BlockSplit{2, 0, 3};
     default: return {2, 2, 2};
   }
 }
@@ -598,7 +599,7 @@ void walk_terms(const Tables &t, int l, int k, int64_t row, Term (&out)[8]) {
 // LDS offsets of the rows of `tops` (nodes k levels above `leaves`, which lie
 // in LDS from row base[i] on): appended to offs, in row order.
 std::string block_offsets(const Tables &t, int l, int k, const Node *tops, int ntops, const Node *leaves,
-                          const std::vector<int> &base, int lead, int tile, std::vector<int32_t> &offs) {
+                          const std::vector<int> &base, int lead, const Pass &ps, std::vector<int32_t> &offs) {
   Term cur[8];
   const int terms = 1 << k;
   for (int j = 0; j < ntops; ++j) {
@@ -611,24 +612,20 @@ std::string block_offsets(const Tables &t, int l, int k, const Node *tops, int n
         const int rl = cur[q].row - x.row0;
         if (rl < 0 || rl >= x.nrows) return "block term row outside its node";
         const int col = lead + x.win - n.win - cur[q].shift;  // column of the top row's first sample
-        if (col < lead || col + n.width > lead + x.width || lead + x.width + tile > kBlockPitch - kBlockTail) return "block term window";
-        offs.push_back((base[i] + rl) * kBlockPitch + col);
+        if (col < lead || col + n.width > lead + x.width || lead + x.width + ps.tile > ps.pitch - (ps.packed ? 2 : 1) * kBlockTail) return "block term window";
+        offs.push_back((base[i] + rl) * ps.pitch + col);
       }
     }
   }
   return "";
 }
 
-std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, int k, bool from_input) {
+std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, int k, bool from_input, bool bytes) {
   Pass ps;
   ps.kind = PassKind::Block;
   ps.from_input = from_input;
   ps.l0 = l0;
   ps.l1 = l0 + k;
-  const BlockSplit sp = block_split(k);
-  ps.k1 = sp.k1;
-  ps.k2 = sp.k2;
-  ps.k3 = sp.k3;
   ps.rows_in = from_input ? t.slots : t.total[l0];
   ps.rows_out = t.total[ps.l1];
   ps.term_offset = static_cast<int64_t>(from_input ? s.iterms.size() : s.terms.size());
@@ -649,6 +646,17 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
     return n;
   };
   while (max_rows > 4 && count_blocks() * tiles < 256) max_rows /= 2;
+  // Packed 16-bit sums: exact while 255 (2^l1 + rows - 1), the largest sum of
+  // uint8 samples, fits, and worth it once the wider tiles fill the GPU.
+  int widest = 0;
+  for (int32_t r : t.rows[ps.l1]) widest = std::max(widest, r);
+  ps.packed = from_input && bytes && 255 * ((int64_t(1) << ps.l1) + widest - 1) <= 65535 &&
+              count_blocks() * ((nt + 447) / 448) >= 1024;
+  ps.pitch = ps.packed ? 2 * kBlockPitch : kBlockPitch;
+  const BlockSplit sp = block_split(k, ps.packed);
+  ps.k1 = sp.k1;
+  ps.k2 = sp.k2;
+  ps.k3 = sp.k3;
   // A node's width with a tile of 0 samples is the spread of its shifts.
   struct Range {
     int sub, r0, nr;
@@ -672,10 +680,11 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
       for (size_t j = a; j < a + (1u << (k - ps.k1)); ++j) lds_rows += tr.nodes[j].nrows;
     }
   }
-  const int lead = from_input ? kBlockLead : 0;
-  ps.tile = (kBlockPitch - kBlockTail - spread - lead) / 32 * 32;
+  const int lead = (from_input ? kBlockLead : 0) * (ps.packed ? 2 : 1);
+  ps.tile = (ps.pitch - (ps.packed ? 2 : 1) * kBlockTail - spread - lead) / 32 * 32;
   if (ps.tile < 128) return "block shifts spread too far";
-  if (from_input && static_cast<int64_t>(blocks.size()) * ((nt + ps.tile - 1) / ps.tile) >= 4096) ps.tiles_per_wg = 2;
+  if (from_input && static_cast<int64_t>(blocks.size()) * ((nt + ps.tile - 1) / ps.tile) >= (ps.packed ? 8192 : 4096))
+    ps.tiles_per_wg = 2;
   Term cur[8];
   const int terms1 = 1 << ps.k1;
   std::vector<int> base_a, base_b;
@@ -733,14 +742,14 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
       const Node *nb = level(ps.k1 + ps.k2);
       const int count_b = 1 << ps.k3;
       rows_b = bases(nb, count_b, base_b);
-      err = block_offsets(t, l0 + ps.k1 + ps.k2, ps.k2, nb, count_b, na, base_a, lead, ps.tile, s.block_offs);
+      err = block_offsets(t, l0 + ps.k1 + ps.k2, ps.k2, nb, count_b, na, base_a, lead, ps, s.block_offs);
       if (!err.empty()) return err;
       below = nb;
       base = &base_b;
     }
     head[3] = rows_b;
     head[4] = static_cast<int32_t>(s.block_offs.size() - ps.offs_offset);
-    err = block_offsets(t, ps.l1, ps.k3, level(k), 1, below, *base, ps.k2 > 0 ? 0 : lead, ps.tile, s.block_offs);
+    err = block_offsets(t, ps.l1, ps.k3, level(k), 1, below, *base, ps.k2 > 0 ? 0 : lead, ps, s.block_offs);
     if (!err.empty()) return err;
     head[5] = b.nr;
     head[6] = static_cast<int32_t>(t.row_off[ps.l1][b.sub] + b.r0);
@@ -757,7 +766,7 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
 
 } // namespace
 
-std::string build_block_schedule(Schedule &s, const Tables &t, int64_t nt, bool search) {
+std::string build_block_schedule(Schedule &s, const Tables &t, int64_t nt, bool search, bool bytes) {
   s = Schedule();
   const int L = search ? t.levels - 3 : t.levels;  // iterations of the block passes
   if (L < 3) return "fewer than three iterations";
@@ -768,7 +777,7 @@ std::string build_block_schedule(Schedule &s, const Tables &t, int64_t nt, bool 
   int l0 = 0;
   for (int i = 0; i < passes; ++i) {
     const int k = (L - l0 + passes - i - 1) / (passes - i);
-    const std::string err = build_block_pass(s, t, nt, l0, k, i == 0 && !s.init_separate);
+    const std::string err = build_block_pass(s, t, nt, l0, k, i == 0 && !s.init_separate, bytes);
     if (!err.empty()) return err;
     l0 += k;
   }

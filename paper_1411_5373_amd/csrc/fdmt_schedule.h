@@ -87,6 +87,8 @@ struct Pass {
   int max_chain = 0;        // register pass from the input: longest Option-1 chain of its terms
   int k1 = 0, k2 = 0, k3 = 0;  // Block: iterations of its three stages (k1 + k2 + k3 = l1 - l0, k2 may be 0)
   int rows_a = 0, rows_b = 0;  // Block: most LDS rows of any block after stage 1 and stage 2
+  int pitch = 0;               // Block: samples of an LDS row (kBlockPitch, or twice that when packed)
+  bool packed = false;         // Block: uint8 input, LDS holds 16-bit sums, two per word
   int tiles_per_wg = 1;        // Block: consecutive time tiles of a workgroup
   int64_t term_count = 0;      // Block: stage-1 terms of the pass
   int64_t offs_offset = 0;     // Block: first LDS offset in Schedule::block_offs (heads: head_offset)
@@ -100,15 +102,17 @@ struct Pass {
 //   stage 2: (k2 > 0) each row of its nodes at level l0 + k1 + k2, from 2^k2
 //            rows of A, into LDS area B;
 //   stage 3: each output row, from 2^k3 rows of B (of A when k2 = 0).
-// Every LDS row holds kBlockPitch samples: column c of a row of a node whose
+// Every LDS row holds `pitch` samples: column c of a row of a node whose
 // window is `win` is time T0 - win + c. Columns past the node's own width are
-// computed too and never used.
+// computed too and never used. A first pass from uint8 input whose sums all
+// stay below 2^16 packs two samples per word, 512 per row.
 constexpr int kBlockPitch = 256;
 // Columns at the start of a row of area A that a pass from the input does not
-// use: the samples its Option-1 chains reach back over.
+// use: the samples its Option-1 chains reach back over (twice as many packed).
 constexpr int kBlockLead = 4;
 // Columns at the end of a row of area A that no pass uses: loads of narrow
-// types take the samples past a lane's words from the next lane.
+// types take the samples past a lane's words from the next lane (twice as many
+// packed).
 constexpr int kBlockTail = 4;
 // Per block: [0] first stage-1 term (pass-relative), [1] rows of A, [2] first
 // stage-2 offset, [3] rows of B, [4] first stage-3 offset, [5] output rows,
@@ -164,9 +168,9 @@ std::string build_schedule(Schedule &s, const Tables &t, const ScheduleParams &p
 
 // The schedule of block passes (see kBlockPitch) for records of nt samples.
 // With `search` the last three iterations are a register gather, the form that
-// can run the boxcar search. Returns "" on success, else why the tables do not
+// can run the boxcar search; `bytes` is uint8 input (sums may be packed). Returns "" on success, else why the tables do not
 // suit it.
-std::string build_block_schedule(Schedule &s, const Tables &t, int64_t nt, bool search);
+std::string build_block_schedule(Schedule &s, const Tables &t, int64_t nt, bool search, bool bytes);
 
 // ---------------------------------------------------------------------------
 // Adjoint schedule. Each pass maps plane l_hi (the gradient of the output when

@@ -133,3 +133,19 @@ def test_graph_replays():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, ref)
+
+
+@pytest.mark.parametrize("form", ["u8", "u8i"])
+@pytest.mark.parametrize("nf,nt,nd,off", [(8, 300001, 20, 0), (16, 262144, 30, 1), (32, 200003, 128, 2), (64, 131075, 64, 3),
+                                          (128, 131000, 200, 0), (500, 70001, 120, 1), (1000, 60000, 1000, 0),
+                                          (2048, 50007, 400, 3)])
+def test_packed_sums(form, nf, nt, nd, off):
+    """uint8 input long enough for the first pass to pack two 16-bit sums per
+    word (3 to 6 iterations, into uint16 planes or straight to the output),
+    from every byte alignment; the largest input value, so that any carry
+    between the halves would show."""
+    p, q = _pair(nf, nt, nd, form)
+    x = _input((off + nf * nt,), torch.uint8, nf)
+    x[: x.numel() // 2] = 255
+    x = x[off:].view(nf, nt)
+    assert torch.equal(p.forward(x), q.forward(x.clone()))
