@@ -440,6 +440,7 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
       };
       if (ps.from_input) {
         const int64_t eb = o.in_dtype == FDMT_U8 ? 1 : o.in_dtype == FDMT_F16 ? 2 : 4;
+        p.block_iplaces.reserve(p.fwd.iterms.size());
         for (const fdmt::InTerm &x : p.fwd.iterms) {
           fdmt::InTerm y = x;
           place((x.ch * nt - x.shift) * eb, y.ch, y.shift);

@@ -25,24 +25,27 @@ struct Tree {
 // Builds the tree of a block and its LDS layout; levels i = 0..k of the pass.
 Tree build_tree(const Tables &t, bool from_input, int l0, int l1, int sub, int r0, int nr, int tile) {
   const int k = l1 - l0;
-  std::vector<std::vector<Node>> lv(k + 1);
-  lv[k].push_back(Node{static_cast<int32_t>(t.row_off[l1][sub] + r0), nr, 0, tile, 0, sub, 0, 0});
+  Tree tr;
+  tr.nodes.resize((size_t(2) << k) - 1);
+  // the 2^(k-i) nodes of level i
+  const auto level = [&](int i) { return tr.nodes.data() + ((2 << k) - (2 << (k - i))); };
+  *level(k) = Node{static_cast<int32_t>(t.row_off[l1][sub] + r0), nr, 0, tile, 0, sub, 0, 0};
   for (int i = k; i >= 1; --i) {
     const int l = l0 + i;
-    lv[i - 1].resize(lv[i].size() * 2);
-    for (size_t j = 0; j < lv[i].size(); ++j) {
-      const Node &n = lv[i][j];
+    for (int j = 0; j < 1 << (k - i); ++j) {
+      const Node &n = level(i)[j];
       const MergeRow &a = t.merge[l][n.row0];
       const MergeRow &b = t.merge[l][n.row0 + n.nrows - 1];
-      lv[i - 1][2 * j] = Node{a.lo, b.lo - a.lo + 1, n.win, n.width, 0, 2 * n.sub, 0, 0};
-      lv[i - 1][2 * j + 1] =
+      level(i - 1)[2 * j] = Node{a.lo, b.lo - a.lo + 1, n.win, n.width, 0, 2 * n.sub, 0, 0};
+      level(i - 1)[2 * j + 1] =
           Node{a.hi, b.hi - a.hi + 1, n.win + b.s, n.width + (b.s - a.s), 0, 2 * n.sub + 1, 0, 0};
     }
   }
   if (from_input) {
     // Leaves become staged input rows: the Option-1 chain of partial-sum row d
     // reads d samples further back, so the window grows by the largest d.
-    for (Node &n : lv[0]) {
+    for (int j = 0; j < 1 << k; ++j) {
+      Node &n = level(0)[j];
       const int ch = n.sub;
       const int d_last = n.row0 + n.nrows - 1 - t.leaf_off[ch];
       n.win += d_last;
@@ -51,17 +54,16 @@ Tree build_tree(const Tables &t, bool from_input, int l0, int l1, int sub, int r
       n.nrows = 1;
     }
   }
-  Tree tr;
   for (int i = 0; i <= k; ++i) {
     int off = 0, cum = 0;
-    for (Node &n : lv[i]) {
+    for (int j = 0; j < 1 << (k - i); ++j) {
+      Node &n = level(i)[j];
       n.lds = i < k ? off : 0;
       n.rowcum = cum;
       off += n.nrows * n.width;
       cum += n.nrows;
     }
     if (i < k) tr.need[i & 1] = std::max(tr.need[i & 1], off);
-    tr.nodes.insert(tr.nodes.end(), lv[i].begin(), lv[i].end());
   }
   return tr;
 }
@@ -612,7 +614,9 @@ std::string block_offsets(const Tables &t, int l, int k, const Node *tops, int n
         const int rl = cur[q].row - x.row0;
         if (rl < 0 || rl >= x.nrows) return "block term row outside its node";
         const int col = lead + x.win - n.win - cur[q].shift;  // column of the top row's first sample
-        if (col < lead || col + n.width > lead + x.width || lead + x.width + ps.tile > ps.pitch - (ps.packed ? 2 : 1) * kBlockTail) return "block term window";
+        if (col < lead || col + n.width > lead + x.width ||
+            lead + x.width + ps.tile > ps.pitch - (ps.packed ? 2 : 1) * kBlockTail)
+          return "block term window";
         offs.push_back((base[i] + rl) * ps.pitch + col);
       }
     }
