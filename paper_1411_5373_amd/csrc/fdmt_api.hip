@@ -391,6 +391,12 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
       return fail(FDMT_E_NOMEM, "host allocation of the adjoint schedule failed");
     }
   }
+  // The in-pass search after block passes: two runs per lane (Nf=4096, Nt=65536,
+  // Nd=2048: 2.44 ms against 3.63 ms with one); with 4 rows per workgroup one run
+  // per lane, whose 2048 threads send the search after the transform (1.07 ms).
+  if (!p.fwd.passes.empty() && p.fwd.passes[0].kind == fdmt::PassKind::Block && o.search_rows > 0 &&
+      o.search_rows < 4 && !o.gather_vecs && !p.adj.passes.empty() && p.adj.passes[0].block)
+    p.gather_vecs = 2;
   // uint16 planes between two cache gathers of a uint8-input plan: plane l
   // sums at most 2^l + dt input samples per element (one per channel plus the
   // chain lengths), so it is exact in 16 bits while 255 * (2^l + rows - 1)
