@@ -51,6 +51,8 @@ KERNEL_SOURCES = ("paper_1411_5373_amd/csrc/fdmt_kernels.hip",
                   "paper_1411_5373_amd/csrc/fdmt_gather.hip",
                   "paper_1411_5373_amd/csrc/fdmt_narrow.hip",
                   "paper_1411_5373_amd/csrc/fdmt_adjoint.hip",
+                  "paper_1411_5373_amd/csrc/fdmt_block.hip",
+                  "paper_1411_5373_amd/csrc/fdmt_adjoint_block.hip",
                   "paper_1411_5373_amd/csrc/fdmt_device.h",
                   "paper_1411_5373_amd/csrc/fdmt_launch.h",
                   "paper_1411_5373_amd/csrc/fdmt_schedule.cpp",

@@ -8,7 +8,10 @@ only speed, so the tuner compares times alone. Forward and adjoint are tuned
 separately: the forward's pass structure first, at one workgroup shape, then
 the workgroup shapes of its first and later passes; the adjoint's depths,
 last-pass shape and work order for each row count. The one field they share
-(samples per lane) is chosen to minimise their sum.
+(samples per lane) is chosen to minimise their sum. The default schedules
+(block passes, no options) are candidates too: the forward's beside any
+adjoint, the adjoint's beside the forward's default, since the fields of a
+forward gather also select gathers for the adjoint.
 
 Cache key: GPU architecture, Nf, Nd, band, the delay law's power when it is
 not -2, input and accumulation dtypes and Nt rounded up to a power of two.
@@ -245,6 +248,9 @@ def tune(nf, nt, nd, f_min, f_max, in_dtype=torch.float32, acc_dtype=torch.float
     def make_adj(**o):
         return B.Plan(nf, nt, nd, f_min, f_max, in_dtype=acc_dtype, acc_dtype=acc_dtype, gamma=gamma, **o)
 
+    fwd_default, adj_default = timed("forward", {}, make_fwd), timed("adjoint", {}, make_adj)
+    if fwd_default is not None and adj_default is not None:
+        best = {"options": {}, "forward_ms": round(fwd_default, 4), "adjoint_ms": round(adj_default, 4)}
     for vecs in GATHER_VECS:
         # forward: the pass structure at one workgroup shape, then the shapes
         fwd_best, adj_best = None, None
@@ -262,6 +268,8 @@ def tune(nf, nt, nd, f_min, f_max, in_dtype=torch.float32, acc_dtype=torch.float
                 ms = timed("forward", opts, make_fwd)
                 if ms is not None and ms < fwd_best[0]:
                     fwd_best = (ms, opts)
+        if fwd_default is not None and (fwd_best is None or fwd_default < fwd_best[0]):
+            fwd_best = (fwd_default, {})  # the adjoint's fields leave it in place
         # adjoint: depths, last-pass shape and work order per row count
         for rows in GATHER_ROWS:
             for cand in adjoint_candidates(rows):
