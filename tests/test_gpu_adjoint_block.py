@@ -8,7 +8,7 @@ batches, and a large smallest delay."""
 import numpy as np
 import pytest
 
-from oracle import fdmt_adjoint as oadj
+from oracle import build_tables, fdmt_adjoint as oadj
 
 pytestmark = pytest.mark.gpu
 
@@ -88,3 +88,24 @@ def test_unaligned_gradient():
     q = F.Plan(nf, nt, nd, 1.2, 1.6, unfused=True)
     g = _grad((3 + nd * nt,), torch.float32, 1)[3:].view(nd, nt)
     assert torch.equal(p.adjoint(g), q.adjoint(g.clone()))
+
+
+@pytest.mark.parametrize("nt", [5, 255, 1024, 1300, 3001])
+@pytest.mark.parametrize("nd", [30, 60, 68, 130, 250])
+@pytest.mark.parametrize("dtype,d_min", [(torch.float32, 0), (torch.float32, 77), (torch.int32, 0)])
+def test_long_chains(nd, nt, dtype, d_min):
+    """The separate initialisation's transpose: chains around its chunk of 16
+    samples, records around its waves' 256, against the oracle's order."""
+    p = F.Plan(4, nt, nd, 1.2, 1.6, in_dtype=dtype, acc_dtype=dtype, d_min=d_min)
+    g = _grad((2, nd, nt), dtype, nd + nt)
+    y = p.adjoint(g)
+    t = build_tables(4, nd, 1.2, 1.6, d_min=d_min)
+    for b in range(2):
+        ref = oadj(g[b].cpu().numpy(), 1.2, 1.6, 4, tables=t, acc=np.int32 if dtype == torch.int32 else np.float32)
+        np.testing.assert_array_equal(y[b].cpu().numpy(), ref)
+    lengths = [nt, 0, 700, 1 + nt // 2]
+    r = F.RaggedPlan(p, lengths)
+    packed = torch.cat([_grad((nd, n), dtype, n).flatten() for n in lengths])
+    for n, gb, xb in zip(lengths, r.unpack(packed, nd), r.unpack(r.adjoint(packed), 4)):
+        ref = oadj(gb.cpu().numpy(), 1.2, 1.6, 4, tables=t, acc=np.int32 if dtype == torch.int32 else np.float32)
+        np.testing.assert_array_equal(xb.cpu().numpy(), ref)
