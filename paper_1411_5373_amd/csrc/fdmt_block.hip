@@ -116,6 +116,7 @@ struct BlockArgs {
   int32_t nt, nblocks, tile, rows_a;
   int32_t tiles_per_wg;  // consecutive time tiles of a workgroup
   int32_t streaming;  // output not read again by this call: non-temporal stores
+  int32_t turn;       // see xcd_turned_order()
   int64_t src_stride, src_bstride, dst_stride, dst_bstride;
 };
 
@@ -184,7 +185,8 @@ __global__ __launch_bounds__(kBlockThreads, 8) void block_pass_kernel(const Tsrc
   Tacc *area_a = reinterpret_cast<Tacc *>(lds_raw);
   Tacc *area_b = area_a + a.rows_a * kBlockPitch;
   const int wave = uniform(threadIdx.x / 64), lane = threadIdx.x % 64;
-  const int block = xcd_local_order(blockIdx.x, a.nblocks);
+  const int block = FROM_INPUT && !RAGGED ? xcd_turned_order(blockIdx.x, a.nblocks, a.turn)
+                                          : xcd_local_order(blockIdx.x, a.nblocks);
   BeamSpan bs = beam_span<RAGGED>(rg, a.nt, a.src_stride, a.src_bstride, a.dst_stride, a.dst_bstride);
   if (!RAGGED && rg.reverse) bs.tile = static_cast<int>(gridDim.y) - 1 - bs.tile;
   const int nt = bs.nt;
@@ -540,6 +542,13 @@ hipError_t launch_block(const BlockLaunch &g, const Tsrc *src, Tdst *dst) {
   a.nblocks = ps.nblocks;
   a.tile = ps.tile;
   a.tiles_per_wg = ps.tiles_per_wg;
+  // Uniform batches from the input, where blocks of many sub-bands run over many
+  // tiles, move on every 16 tiles: Nf=4096, Nt=65536 FP32 0.468 -> 0.447 ms, batch
+  // 16 of Nf=1024, Nt=16384 0.652 -> 0.619 ms. Every tile or every 4 loses the
+  // L2's overlap of neighbouring tiles (0.466, 0.450 ms). A pass from a plane
+  // reads most of it again in the next tile and got slower (up to 8%, with the
+  // test alone in its code 5%), packed and ragged passes gained nothing.
+  a.turn = FROM_INPUT && !ps.packed && ps.nblocks % 8 == 0 && ps.nblocks >= 64 && g.grid.y * g.grid.z >= 128 ? 4 : 0;
   a.rows_a = ps.rows_a;
   a.streaming = g.streaming;
   a.src_stride = g.src_stride;

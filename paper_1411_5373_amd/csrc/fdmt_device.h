@@ -94,6 +94,16 @@ __device__ __forceinline__ int xcd_local_order(int id, int n) {
   return x * q + (x < r ? x : r) + slot;
 }
 
+// The same for a grid {n blocks, time tiles, beams} whose blocks are unequal
+// work (the rows of some sub-bands have more terms): with n a multiple of 8
+// every XCD would have its own blocks in every tile and the slowest set the
+// time. turn = k > 0 (n a multiple of 8) hands each range of blocks on to the
+// next XCD every 2^k tiles; 0: never.
+__device__ __forceinline__ int xcd_turned_order(int id, int n, int turn) {
+  if (turn > 0) id = (id & ~7) | ((id + static_cast<int>((blockIdx.y + gridDim.y * blockIdx.z) >> turn)) & 7);
+  return xcd_local_order(id, n);
+}
+
 
 // Place of a wave in a register-gather workgroup of blockDim.x threads that
 // holds rows_per_wg rows side by side, col_waves waves along time per row.
