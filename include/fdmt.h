@@ -88,9 +88,10 @@ typedef enum {
                                     same results; used to cross-check the fused one) */
 #define FDMT_PLAN_WIDE_PLANES 0x4u /* keep every intermediate plane in the accumulation
                                       dtype. By default a uint8-input plan stores the
-                                      planes between two cache gathers as uint16 while
-                                      every sum on them is below 2^16 (exact integers,
-                                      same results, half the bytes) */
+                                      planes between two gather or block passes as
+                                      uint16, and a first block pass holds its sums as
+                                      uint16, while every sum on them is below 2^16
+                                      (exact integers, same results, half the bytes) */
 #define FDMT_PLAN_FFT 0x8u         /* also build the FFT-FDMT state (Sec. 5, Algorithm 2)
                                       for fdmt_forward_fft(): FP32 accumulation only, the
                                       padded FFT length (the smallest 2^a 3^b 5^c >=
@@ -98,7 +99,16 @@ typedef enum {
                                       table and hipFFT plans with the plan */
 
 /* Options of a plan. Zero in any schedule field selects the built-in default;
- * schedule fields change only the kernel schedule, never the results. */
+ * schedule fields change only the kernel schedule, never the results.
+ *
+ * With every forward schedule field zero (first_levels .. gather_rows,
+ * gather_threads, first_rows, first_threads) the forward runs in block passes, up
+ * to six iterations per launch; with every adjoint field, gather_rows and
+ * gather_vecs zero the adjoint does, up to four. A nonzero field selects the other
+ * forms for its direction, whose own defaults the comments below give; they also
+ * run shapes that block passes do not cover (fewer than three iterations, or two
+ * for the adjoint; shifts within a block that spread past its window; an Nt of
+ * more than 65535 tiles). */
 typedef struct {
   int32_t in_dtype;       /* fdmt_dtype_t of the forward input */
   int32_t acc_dtype;      /* FDMT_F32 or FDMT_I32 */
@@ -135,9 +145,9 @@ typedef struct {
                              different range of dispersions): channel k's input is
                              delayed by pre_k = round(d_min * phi(c_k)), phi the fraction
                              of the band delay at its centre c_k, so output row dt
-                             follows delay d_min + dt. Needs the first pass to gather from
-                             the input (first_kernel 3, the default when d_min > 0) or
-                             the unfused schedule. Changes the results */
+                             follows delay d_min + dt. Needs block passes, a first pass that
+                             gathers from the input (first_kernel 3, the default of the
+                             other forms when d_min > 0) or the unfused schedule. Changes the results */
   uint32_t adjoint_tile_major; /* bit i set: adjoint gather pass i (launch order) runs each row
                                   group's time tiles back to back on one XCD instead of all
                                   groups of a tile together; suits passes whose leaves sit at
@@ -179,9 +189,9 @@ typedef struct {
 /* Build a plan: the delay tables of every iteration (Sec. 4: the rows each
  * sub-band needs are fixed before any data is seen) and the kernel schedule, then upload
  * the tables to the current HIP device.
- *   nf     channels, 1 <= nf <= 65536 (not a power of two: the forward first
- *          copies the input into the workspace with zero rows up to the next
- *          power of two, and every schedule runs on that copy)
+ *   nf     channels, 1 <= nf <= 65536 (not a power of two: schedules other than
+ *          block passes first copy the input into the workspace with zero rows
+ *          up to the next power of two and run on that copy)
  *   nt     samples per beam, 1 <= nt <= 2^31 - 1
  *   nd     delay trials (output rows), 1 <= nd <= 65536
  *   f_min, f_max  band edges in any one unit, 0 < f_min < f_max
@@ -287,7 +297,7 @@ fdmt_status_t fdmt_plan_destroy(fdmt_plan_t p);
  * step of a transform is one launch over all beams (a further launch per
  * 65535 time tiles of that step), so the beam count does not multiply the
  * launch count. Beam b has nt[b] samples (0 allowed); the delay tables and
- * schedule are the plan's, whose own Nt is not used. Results per beam are
+ * schedule are the plan's, whose own Nt only shapes its schedule. Results per beam are
  * bit-identical to fdmt_forward()/fdmt_adjoint() of a plan with Nt = nt[b].
  *
  * Packed layout (dense, time fastest): beam b's [rows][nt[b]] block starts at
@@ -301,10 +311,10 @@ fdmt_status_t fdmt_plan_destroy(fdmt_plan_t p);
  *
  * Each step is an ordinary launch over the flattened (beam, time tile) map,
  * not a persistent work-queue kernel: on MI355X, for 256 beams of Nf = 1024,
- * Nd = 512 and 3.1 M samples in all, the gaps between a forward's four
- * launches add about 0.01 ms to its 14 ms, and two half batches cost at most
- * 0.05 ms more than one call, so a single resident kernel could save well
- * under 1% while adding spin waits between passes.
+ * Nd = 512 and 3.1 M samples in all, the gap between a forward's two launches
+ * adds at most 0.06 ms to its 8.9 ms, and two half batches cost no more than one
+ * call, so a single resident kernel could save well under 1% while adding spin
+ * waits between passes.
  *
  * fdmt_ragged_plan errors: FDMT_E_INVALID (NULL pointer, nbeams < 1, an nt[b]
  * outside [0, 2^31 - 1], device mismatch), FDMT_E_UNSUPPORTED (host-only plan,

@@ -342,7 +342,7 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
     if (o.later_kernel) sp.later_kind = kinds[o.later_kernel];
     // Block passes (fdmt_block.hip) are the default: at every shape measured
     // they beat the other forms, also the tuned register gathers, from Nf=64,
-    // Nt=1024 (8 us against 23 us) to Nf=4096, Nt=65536 (0.61 ms against 0.78 ms,
+    // Nt=1024 (8 us against 23 us) to Nf=4096, Nt=65536 (0.56 ms against 0.78 ms,
     // uint8). A nonzero forward schedule field asks for another form, and these
     // also run what block passes do not cover: fewer than three iterations,
     // block shifts that spread past half a tile, or an Nt with more block tiles

@@ -17,9 +17,9 @@
 // are no faster, and four or eight tiles slower).
 //
 // Measured (one MI355X, register gathers -> block passes): Nf=4096, Nt=65536,
-// Nd=2048 uint8 0.776 -> 0.614 ms, FP32 1.238 -> 0.883 ms; batch 16 of
-// Nf=1024, Nt=16384, Nd=1024 FP32 2.120 -> 1.285 ms (3.4 TB/s of plane
-// traffic); Nf=1000, Nt=40001, Nd=900 uint8 0.240 -> 0.111 ms; Nf=64, Nt=1024,
+// Nd=2048 uint8 0.776 -> 0.562 ms, FP32 1.238 -> 0.858 ms; batch 16 of
+// Nf=1024, Nt=16384, Nd=1024 FP32 2.120 -> 1.229 ms (3.5 TB/s of plane
+// traffic); Nf=1000, Nt=40001, Nd=900 uint8 0.240 -> 0.098 ms; Nf=64, Nt=1024,
 // Nd=64 FP32 0.023 -> 0.008 ms (one launch). What bounds a pass now is its
 // instruction stream and the latency between its stages: without loads and
 // stores a six-iteration pass of the first workload still takes 0.18 ms, its
