@@ -195,7 +195,12 @@ __device__ __forceinline__ void box_stats(const Float4 (&v)[kBoxChunks], int nva
   for (int c = 0; c < kBoxChunks; ++c) {
     if (at != INT32_MAX) continue;
     bool here = top[c] == peak;
-    if (!FULL) here = here && 256 * c + 4 * lane < nvalid;
+    if (!FULL) {
+      // a lane without a valid sample, or with NaNs alone, has the -inf its top started at
+      here = false;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) here = here || (256 * c + 4 * lane + i < nvalid && v[c][i] == peak);
+    }
     const uint64_t lanes = __builtin_amdgcn_ballot_w64(here);
     if (lanes) {
       int i = 3;
