@@ -357,8 +357,8 @@ fdmt_status_t fdmt_ragged_destroy(fdmt_ragged_t r);
  * summed in FP32 as b_2w[t] = b_w[t] + b_w[t-w] from b_1 = y, and reports its
  * largest value `peak`, the first t where it occurs, the mean and (population)
  * standard deviation of b_w over t = 0..nt-1, accumulated in FP64, and
- * snr = (peak - mean) / stdev (0 when stdev is 0). NaN samples are never a
- * peak. */
+ * snr = (peak - mean) / stdev (0 when stdev is 0). A NaN sum is never a peak;
+ * a row of NaN sums has peak -inf and t = 2^31 - 1. */
 typedef struct {
   float peak;
   int32_t t;
@@ -370,7 +370,8 @@ typedef struct {
 /* A candidate event of fdmt_forward_search(): in beam `beam`, row `dt`, the
  * width-2^width_log2 running sum's largest value `peak` inside one block of
  * 2048 samples (first at time t), with snr = (peak - mean) / stdev against
- * the row's statistics of that width over the whole record. */
+ * the row's statistics of that width over the whole record. A block of NaN
+ * sums has none. */
 typedef struct {
   int32_t beam;
   int32_t dt;

@@ -17,7 +17,7 @@ constexpr int kBoxMaxLog2 = 10;  // widths up to 2^10 samples
 struct BoxPartial {
   double sum, sumsq;  // of b_w over the tile's samples
   float peak;         // largest b_w
-  int32_t t;          // first time of it
+  int32_t t;          // first time of it, INT32_MAX (peak -inf): every sum is a NaN
 };
 
 size_t boxcar_workspace_bytes(int32_t batch, int32_t nd, int64_t nt, int32_t max_log2);

@@ -226,8 +226,8 @@ __device__ __forceinline__ void box_widths(Float4 (&v)[kBoxChunks], BoxHistory &
   int at;
   box_stats<FULL>(v, nvalid, lane, sums.s[J], sums.q[J], peak, at);
   if (lane == 0) {
-    // unsigned: a tile without a peak keeps INT32_MAX past t0
-    p[J * width_stride] = BoxPartial{0.0, 0.0, peak, static_cast<int32_t>(static_cast<uint32_t>(t0) + static_cast<uint32_t>(at))};
+    // a tile without a peak keeps INT32_MAX: the kernels below know it by that
+    p[J * width_stride] = BoxPartial{0.0, 0.0, peak, at == INT32_MAX ? INT32_MAX : t0 + at};
   }
   if constexpr (J < M) {
     // keep the widths apart: mixed by the scheduler, their values are all live
