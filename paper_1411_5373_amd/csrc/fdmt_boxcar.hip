@@ -390,7 +390,10 @@ __global__ __launch_bounds__(kBoxThreads) void boxcar_edge_kernel(const float *_
 // found (optional) is the candidate count, cleared for the kernel after this.
 // One thread per row walked 32 partials one after another: 14 us for 9 widths
 // of 2048 rows, now 6 us.
+// A launch takes fewer than 2^32 threads, so more than kCombineBlocks blocks'
+// worth of results go round the grid.
 constexpr int kCombineLanes = 16;
+constexpr int64_t kCombineBlocks = 1 << 20;
 __global__ __launch_bounds__(256) void boxcar_combine_kernel(const BoxPartial *__restrict__ part,
                                                              fdmt_boxcar_t *__restrict__ out, int64_t nt,
                                                              int32_t ntiles, int64_t count,
@@ -398,45 +401,46 @@ __global__ __launch_bounds__(256) void boxcar_combine_kernel(const BoxPartial *_
                                                              int32_t *__restrict__ found) {
   const int64_t id = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (found && id == 0) *found = 0;
-  const int64_t k = id / kCombineLanes;
-  if (k >= count) return;  // whole groups of lanes
   const int lane = static_cast<int>(id % kCombineLanes);
-  const BoxPartial *p = part + k * ntiles;
-  double s = 0.0, q = 0.0;
-  float best = -__builtin_inff();
-  int best_t = INT32_MAX;
-  for (int i = lane; i < ntiles; i += kCombineLanes) {
-    const BoxPartial x = p[i];
-    s += x.sum;
-    q += x.sumsq;
-    if (better(x.peak, x.t, best, best_t)) {
-      best = x.peak;
-      best_t = x.t;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x / kCombineLanes;
+  for (int64_t k = id / kCombineLanes; k < count; k += stride) {  // the same for a whole group of lanes
+    const BoxPartial *p = part + k * ntiles;
+    double s = 0.0, q = 0.0;
+    float best = -__builtin_inff();
+    int best_t = INT32_MAX;
+    for (int i = lane; i < ntiles; i += kCombineLanes) {
+      const BoxPartial x = p[i];
+      s += x.sum;
+      q += x.sumsq;
+      if (better(x.peak, x.t, best, best_t)) {
+        best = x.peak;
+        best_t = x.t;
+      }
     }
-  }
 #pragma unroll
-  for (int m = kCombineLanes / 2; m >= 1; m >>= 1) {
-    s += __shfl_xor(s, m, kCombineLanes);
-    q += __shfl_xor(q, m, kCombineLanes);
-    const float ov = __shfl_xor(best, m, kCombineLanes);
-    const int ot = __shfl_xor(best_t, m, kCombineLanes);
-    if (better(ov, ot, best, best_t)) {
-      best = ov;
-      best_t = ot;
+    for (int m = kCombineLanes / 2; m >= 1; m >>= 1) {
+      s += __shfl_xor(s, m, kCombineLanes);
+      q += __shfl_xor(q, m, kCombineLanes);
+      const float ov = __shfl_xor(best, m, kCombineLanes);
+      const int ot = __shfl_xor(best_t, m, kCombineLanes);
+      if (better(ov, ot, best, best_t)) {
+        best = ov;
+        best_t = ot;
+      }
     }
+    if (lane != 0) continue;
+    const double mean = s / static_cast<double>(nt);
+    const double var = q / static_cast<double>(nt) - mean * mean;
+    const double sd = var > 0.0 ? sqrt(var) : 0.0;
+    fdmt_boxcar_t r;
+    r.peak = best;
+    r.t = best_t;
+    r.mean = static_cast<float>(mean);
+    r.stdev = static_cast<float>(sd);
+    r.snr = sd > 0.0 ? static_cast<float>((static_cast<double>(best) - mean) / sd) : 0.0f;
+    out[k] = r;
+    if (mean_sd) mean_sd[k] = make_double2(mean, sd);
   }
-  if (lane != 0) return;
-  const double mean = s / static_cast<double>(nt);
-  const double var = q / static_cast<double>(nt) - mean * mean;
-  const double sd = var > 0.0 ? sqrt(var) : 0.0;
-  fdmt_boxcar_t r;
-  r.peak = best;
-  r.t = best_t;
-  r.mean = static_cast<float>(mean);
-  r.stdev = static_cast<float>(sd);
-  r.snr = sd > 0.0 ? static_cast<float>((static_cast<double>(best) - mean) / sd) : 0.0f;
-  out[k] = r;
-  if (mean_sd) mean_sd[k] = make_double2(mean, sd);
 }
 
 // One thread per (beam, width, row, tile): the tile's peak is a candidate
@@ -533,7 +537,8 @@ hipError_t launch_boxcar_combine(const BoxPartial *part, int32_t batch, int32_t 
                                  fdmt_boxcar_t *out, double2 *mean_sd, int32_t *found, hipStream_t stream) {
   const int64_t ntiles = (nt + kBoxTile - 1) / kBoxTile;
   const int64_t count = static_cast<int64_t>(batch) * (max_log2 + 1) * nd;
-  hipLaunchKernelGGL(boxcar_combine_kernel, dim3(static_cast<unsigned>((count * kCombineLanes + 255) / 256)),
+  const int64_t blocks = (count * kCombineLanes + 255) / 256;
+  hipLaunchKernelGGL(boxcar_combine_kernel, dim3(static_cast<unsigned>(blocks < kCombineBlocks ? blocks : kCombineBlocks)),
                      dim3(256), 0, stream, part, out, nt, static_cast<int32_t>(ntiles), count, mean_sd, found);
   return hipGetLastError();
 }
