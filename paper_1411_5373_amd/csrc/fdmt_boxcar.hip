@@ -151,17 +151,17 @@ __device__ __forceinline__ void box_double(Float4 (&v)[C], BoxHistory &h, float 
   }
 }
 
-// Statistics of one width over a tile: FP64 sums of the lane's samples, and the
-// wave's peak with its first sample (INT32_MAX: no peak, every value a NaN).
-// FULL: every sample counts; else those below nvalid.
-template <bool FULL>
-__device__ __forceinline__ void box_stats(const Float4 (&v)[kBoxChunks], int nvalid, int lane, double &s, double &q,
+// Statistics of one width over a tile of C chunks: FP64 sums of the lane's
+// samples, and the wave's peak with its first sample (INT32_MAX: no peak, every
+// value a NaN). FULL: every sample counts; else those below nvalid.
+template <bool FULL, int C>
+__device__ __forceinline__ void box_stats(const Float4 (&v)[C], int nvalid, int lane, double &s, double &q,
                                           float &peak, int &at) {
-  float top[kBoxChunks];
+  float top[C];
   double s1 = 0.0, q1 = 0.0;
   float best = -__builtin_inff();
 #pragma unroll
-  for (int c = 0; c < kBoxChunks; ++c) {
+  for (int c = 0; c < C; ++c) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       double x = static_cast<double>(v[c][i]);
@@ -192,7 +192,7 @@ __device__ __forceinline__ void box_stats(const Float4 (&v)[kBoxChunks], int nva
   peak = wave_max(best);
   at = INT32_MAX;
 #pragma unroll
-  for (int c = 0; c < kBoxChunks; ++c) {
+  for (int c = 0; c < C; ++c) {
     if (at != INT32_MAX) continue;
     bool here = top[c] == peak;
     if (!FULL) {
@@ -219,8 +219,8 @@ struct BoxSums {
   double s[M + 1] = {}, q[M + 1] = {};
 };
 
-template <int M, int J, bool FULL>
-__device__ __forceinline__ void box_widths(Float4 (&v)[kBoxChunks], BoxHistory &h, float *buf, int lane, int nvalid,
+template <int M, int J, bool FULL, int C>
+__device__ __forceinline__ void box_widths(Float4 (&v)[C], BoxHistory &h, float *buf, int lane, int nvalid,
                                            BoxSums<M> &sums, BoxPartial *p, int64_t width_stride, int32_t t0) {
   float peak;
   int at;
@@ -245,6 +245,25 @@ __device__ __forceinline__ void box_warm(Float4 (&v)[C], BoxHistory &h, float *b
     box_double<J>(v, h, buf, lane);
     box_warm<M, J + 1>(v, h, buf, lane);
   }
+}
+
+// A row's last tile of nvalid samples, at most C chunks (nothing follows that
+// would need its history). Rows of kBoxFew chunks or fewer had the work of a
+// whole tile: 50000 rows of 50 samples with widths 1..32 took 163 us with every
+// width in LDS, 221 us with tiles in registers and now 127 us.
+constexpr int kBoxFew = 2;  // the widest history, 512 samples, takes as many
+template <int M, int C>
+__device__ __forceinline__ void box_last_tile(const float *y, BoxHistory &h, float *buf, int lane, int nvalid,
+                                              BoxSums<M> &sums, BoxPartial *p, int64_t width_stride, int32_t t0) {
+  Float4 v[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int u = 256 * c + 4 * lane + i;
+      v[c][i] = u < nvalid ? y[u] : 0.0f;
+    }
+  box_widths<M, 0, false>(v, h, buf, lane, nvalid, sums, p, width_stride, t0);
 }
 
 // Three waves per SIMD: at four (128 VGPRs) the widest searches spill, 0.36 ms.
@@ -281,16 +300,12 @@ __global__ __launch_bounds__(kBoxThreads, 3) void boxcar_tile_kernel(const float
 #pragma unroll
       for (int c = 0; c < kBoxChunks; ++c) v[c] = *reinterpret_cast<const Float4u *>(y + t0 + 256 * c + 4 * lane);
       box_widths<M, 0, true>(v, h, buf, lane, kBoxTile, sums, p + tile, width_stride, static_cast<int32_t>(t0));
+    } else if (left > 256 * kBoxFew) {
+      box_last_tile<M, kBoxChunks>(y + t0, h, buf, lane, static_cast<int>(left), sums, p + tile, width_stride,
+                                   static_cast<int32_t>(t0));
     } else {
-      const int nvalid = static_cast<int>(left);
-#pragma unroll
-      for (int c = 0; c < kBoxChunks; ++c)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int u = 256 * c + 4 * lane + i;
-          v[c][i] = u < nvalid ? y[t0 + u] : 0.0f;
-        }
-      box_widths<M, 0, false>(v, h, buf, lane, nvalid, sums, p + tile, width_stride, static_cast<int32_t>(t0));
+      box_last_tile<M, kBoxFew>(y + t0, h, buf, lane, static_cast<int>(left), sums, p + tile, width_stride,
+                                static_cast<int32_t>(t0));
     }
   }
   // the span's sums go to its first tile's partials
