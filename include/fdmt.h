@@ -317,7 +317,8 @@ fdmt_status_t fdmt_plan_destroy(fdmt_plan_t p);
  * waits between passes.
  *
  * fdmt_ragged_plan errors: FDMT_E_INVALID (NULL pointer, nbeams < 1, an nt[b]
- * outside [0, 2^31 - 1], device mismatch), FDMT_E_UNSUPPORTED (host-only plan,
+ * outside [0, 2^31 - 1] or so long that d_min, 2 Nd, a time tile and 2^13
+ * samples more pass 2^31 - 1, device mismatch), FDMT_E_UNSUPPORTED (host-only plan,
  * a plan whose passes use the staged-gather kernel, more than 2^31 - 1 padded
  * samples in total), FDMT_E_NOMEM. */
 fdmt_status_t fdmt_ragged_plan(fdmt_ragged_t *out, fdmt_plan_t p, int32_t nbeams, const int64_t *nt);

@@ -761,6 +761,16 @@ fdmt_status_t fdmt_ragged_plan(fdmt_ragged_t *out, fdmt_plan_t p, int32_t nbeams
       if (std::find(widths.begin(), widths.end(), key) == widths.end()) widths.push_back(key);
     }
   }
+  // Sample indices are int32 in the kernels as in a uniform batch (see fdmt_plan),
+  // where the limit on tiles keeps an index past the end in range; here a beam's
+  // last tile may start just below its end, so the widest tile counts too.
+  int64_t widest = 0;
+  for (const auto &w : widths) widest = std::max<int64_t>(widest, w.first);
+  const int64_t longest = INT32_MAX - 8192 - widest - P.tab.d_min - 2 * static_cast<int64_t>(P.tab.nd);
+  for (int32_t b = 0; b < nbeams; ++b)
+    if (nt[b] > longest)
+      return fail(FDMT_E_INVALID, "beam " + std::to_string(b) + ": Nt must be at most " + std::to_string(longest) +
+                                      " (2^31 less d_min, 2 Nd, the widest time tile and 2^13)");
   if (P.flags & FDMT_PLAN_HOST_ONLY)
     return fail(FDMT_E_UNSUPPORTED, "plan was built with FDMT_PLAN_HOST_ONLY");
   auto *h = new (std::nothrow) fdmt_ragged_s;
