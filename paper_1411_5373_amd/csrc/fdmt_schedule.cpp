@@ -991,79 +991,96 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
   // sub-band of no more than `most` rows stays whole: no row is then made twice.
   int most = kAdjBlockRows;
   while (own > 7 && workgroups(ps.pitch) < 256) most = own /= 2;
-  // Ranges, gathered into blocks while their rows fit LDS.
-  struct Piece {
-    size_t first, last;  // outputs
-    int32_t lo, hi;      // rows lo .. hi of plane m
-  };
-  std::vector<Piece> block;
+  // Ranges, gathered into blocks while their rows fit LDS and their outputs'
+  // offsets lie together: a block runs the windows between its smallest and its
+  // largest offset for all of its rows.
+  const int64_t apart = std::max<int64_t>(ps.pitch, nt / 2);
   typedef std::array<int32_t, kAdjBlockHeader> Head;
-  std::vector<Head> heads;
+  struct Block {
+    Head head;
+    int32_t row;  // its first row of plane l_hi
+  };
+  std::vector<Block> blocks;
+  Block block{};
   int block_rows = 0, spread = 0;
   std::vector<AdjLeaf> leaves;
-  std::vector<int32_t> betas;
+  std::vector<AdjBlockLeaf> range;  // the range's stage-1 leaves
+  std::vector<int32_t> starts, betas;
   s.block_leaves1.reserve(s.block_leaves1.size() + static_cast<size_t>(rows) * 6);
   s.block_leaves2.reserve(s.block_leaves2.size() + pool.size());
   s.block_outs.reserve(s.block_outs.size() + outs.size());
   const auto flush = [&]() {
-    if (block.empty()) return;
-    int32_t head[kAdjBlockHeader] = {};
-    head[0] = static_cast<int32_t>(s.block_mids.size() - ps.mid_offset);
-    head[2] = static_cast<int32_t>(s.block_outs.size() - ps.out_offset);
-    int base = 0;
-    for (const Piece &p : block) {
-      // The range's smallest stage-1 shift moves its window instead of its
-      // leaves: every range then reads plane l_hi over one and the same time.
-      int32_t lag = INT32_MAX;
-      const size_t first = s.block_leaves1.size();
-      for (int32_t r = p.lo; r <= p.hi; ++r) {
-        leaves.clear();
-        AdjWalker w{t, l_hi, leaves};
-        w.visit(m, r, 0, 0, 0);
-        s.block_mids.push_back(static_cast<int32_t>(s.block_leaves1.size() - ps.leaf_offset));
-        for (const AdjLeaf &e : leaves) {
-          s.block_leaves1.push_back(AdjBlockLeaf{e.row, 4 * e.shift + e.branch});
-          lag = std::min(lag, e.shift);
-        }
-      }
-      for (size_t j = first; j < s.block_leaves1.size(); ++j) {
-        s.block_leaves1[j].shift4 -= 4 * lag;
-        head[4] = std::max(head[4], s.block_leaves1[j].shift4 >> 2);
-      }
-      // each output sub-band's smallest shift in this range is its offset (the
-      // sub-bands under one of plane m are few and consecutive)
-      const int sub0 = (outs[p.first].sub >> (m - l_lo)) << (m - l_lo);
-      betas.assign(size_t(1) << (m - l_lo), INT32_MAX);
-      for (size_t i = p.first; i < p.last; ++i)
-        for (int32_t x = outs[i].first; x < outs[i].last; ++x)
-          betas[outs[i].sub - sub0] = std::min(betas[outs[i].sub - sub0], pool[x].shift);
-      for (int32_t &b : betas)
-        if (b != INT32_MAX) b -= (b + lag) & (align - 1);
-      for (size_t i = p.first; i < p.last; ++i) {
-        const AdjOutRow &o = outs[i];
-        const int32_t beta = betas[o.sub - sub0];
-        AdjBlockOut b{static_cast<int32_t>(s.block_leaves2.size() - ps.leaf2_offset), 0, o.row, beta + lag};
-        for (int32_t x = o.first; x < o.last; ++x) {
-          const AdjLeaf &e = pool[x];
-          s.block_leaves2.push_back(((base + e.row - p.lo) * ps.pitch + e.shift - beta) * 4 + e.branch);
-          spread = std::max(spread, e.shift - beta);
-        }
-        b.last = static_cast<int32_t>(s.block_leaves2.size() - ps.leaf2_offset);
-        s.block_outs.push_back(b);
-        head[5] = std::max(head[5], beta + lag);
-      }
-      base += p.hi - p.lo + 1;
-    }
-    head[1] = static_cast<int32_t>(s.block_mids.size() - ps.mid_offset) - head[0];
-    head[3] = static_cast<int32_t>(s.block_outs.size() - ps.out_offset) - head[2];
-    head[6] = s.block_leaves1[ps.leaf_offset + s.block_mids[ps.mid_offset + head[0]]].row;
-    heads.push_back(Head{});
-    std::copy(head, head + kAdjBlockHeader, heads.back().begin());
-    ps.rows_mid = std::max(ps.rows_mid, base);
-    ps.extra = std::max(ps.extra, head[5]);
-    ++ps.nblocks;
-    block.clear();
+    if (block_rows == 0) return;
+    block.head[1] = static_cast<int32_t>(s.block_mids.size() - ps.mid_offset) - block.head[0];
+    block.head[3] = static_cast<int32_t>(s.block_outs.size() - ps.out_offset) - block.head[2];
+    blocks.push_back(block);
+    ps.rows_mid = std::max(ps.rows_mid, block_rows);
     block_rows = 0;
+  };
+  // Outputs [first, last), with their rows lo .. hi of plane m.
+  const auto add_range = [&](size_t first, size_t last, int32_t lo, int32_t hi) {
+    // The range's smallest stage-1 shift moves its window instead of its
+    // leaves: every range then reads plane l_hi over one and the same time.
+    int32_t lag = INT32_MAX;
+    range.clear();
+    starts.clear();
+    for (int32_t r = lo; r <= hi; ++r) {
+      leaves.clear();
+      AdjWalker w{t, l_hi, leaves};
+      w.visit(m, r, 0, 0, 0);
+      starts.push_back(static_cast<int32_t>(range.size()));
+      for (const AdjLeaf &e : leaves) {
+        range.push_back(AdjBlockLeaf{e.row, 4 * e.shift + e.branch});
+        lag = std::min(lag, e.shift);
+      }
+    }
+    // each output sub-band's smallest shift in this range is its offset (the
+    // sub-bands under one of plane m are few and consecutive)
+    const int sub0 = (outs[first].sub >> (m - l_lo)) << (m - l_lo);
+    betas.assign(size_t(1) << (m - l_lo), INT32_MAX);
+    for (size_t i = first; i < last; ++i)
+      for (int32_t x = outs[i].first; x < outs[i].last; ++x)
+        betas[outs[i].sub - sub0] = std::min(betas[outs[i].sub - sub0], pool[x].shift);
+    int32_t near = INT32_MAX, far = 0;
+    for (int32_t &b : betas)
+      if (b != INT32_MAX) {
+        b -= (b + lag) & (align - 1);
+        near = std::min(near, b + lag);
+        far = std::max(far, b + lag);
+      }
+    const int have = hi - lo + 1;
+    if (block_rows > 0 && (block_rows + have > kAdjBlockRows || block_rows >= own ||
+                           std::max(block.head[5], far) - std::min(block.head[6], near) > apart))
+      flush();
+    if (block_rows == 0) {
+      block = Block{};
+      block.head[0] = static_cast<int32_t>(s.block_mids.size() - ps.mid_offset);
+      block.head[2] = static_cast<int32_t>(s.block_outs.size() - ps.out_offset);
+      block.head[6] = INT32_MAX;
+      block.row = range[0].row;
+    }
+    const int32_t base = static_cast<int32_t>(s.block_leaves1.size() - ps.leaf_offset);
+    for (int32_t x : starts) s.block_mids.push_back(base + x);
+    for (AdjBlockLeaf e : range) {
+      e.shift4 -= 4 * lag;
+      block.head[4] = std::max(block.head[4], e.shift4 >> 2);
+      s.block_leaves1.push_back(e);
+    }
+    block.head[5] = std::max(block.head[5], far);
+    block.head[6] = std::min(block.head[6], near);
+    for (size_t i = first; i < last; ++i) {
+      const AdjOutRow &o = outs[i];
+      const int32_t beta = betas[o.sub - sub0];
+      AdjBlockOut b{static_cast<int32_t>(s.block_leaves2.size() - ps.leaf2_offset), 0, o.row, beta + lag};
+      for (int32_t x = o.first; x < o.last; ++x) {
+        const AdjLeaf &e = pool[x];
+        s.block_leaves2.push_back(((block_rows + e.row - lo) * ps.pitch + e.shift - beta) * 4 + e.branch);
+        spread = std::max(spread, e.shift - beta);
+      }
+      b.last = static_cast<int32_t>(s.block_leaves2.size() - ps.leaf2_offset);
+      s.block_outs.push_back(b);
+    }
+    block_rows += have;
   };
   for (int x = 0; x < subs; ++x) {
     const int n = t.rows[m][x];
@@ -1072,31 +1089,51 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
     size_t i = out_of[x];
     for (int b = 0; b < parts; ++b) {
       const int32_t end = off + static_cast<int32_t>(static_cast<int64_t>(n) * (b + 1) / parts);
-      Piece p{i, i, INT32_MAX, -1};
+      const size_t first = i;
+      int32_t lo = INT32_MAX, hi = -1;
       for (; i < out_of[x + 1] && outs[i].lead < end; ++i)
         for (int32_t y = outs[i].first; y < outs[i].last; ++y) {
-          p.lo = std::min(p.lo, pool[y].row);
-          p.hi = std::max(p.hi, pool[y].row);
+          lo = std::min(lo, pool[y].row);
+          hi = std::max(hi, pool[y].row);
         }
-      p.last = i;
-      if (p.first == p.last) continue;
-      const int have = p.hi - p.lo + 1;
-      if (have > kAdjBlockRows) return "block rows do not fit LDS";
-      if (block_rows + have > kAdjBlockRows || block_rows >= own) flush();
-      block.push_back(p);
-      block_rows += have;
+      if (first == i) continue;
+      if (hi - lo + 1 > kAdjBlockRows) return "block rows do not fit LDS";
+      add_range(first, i, lo, hi);
     }
   }
   flush();
   s.block_mids.push_back(static_cast<int32_t>(s.block_leaves1.size() - ps.leaf_offset));
   // blocks of several sub-bands read the same rows of plane l_hi: run them next
   // to each other, on one XCD
-  std::stable_sort(heads.begin(), heads.end(), [](const Head &a, const Head &b) { return a[6] < b[6]; });
-  for (const Head &h : heads) s.block_heads.insert(s.block_heads.end(), h.begin(), h.end());
+  std::stable_sort(blocks.begin(), blocks.end(), [](const Block &a, const Block &b) { return a.row < b.row; });
   ps.leaf1_count = static_cast<int64_t>(s.block_leaves1.size()) - ps.leaf_offset;
   ps.leaves = ps.leaf1_count;
   ps.tile = (ps.pitch - spread) / align * align;
   if (ps.tile < 128 || spread > 128) return "block shifts spread too far";
+  // T0 = 0 is the same time in every block where the offsets are those of the
+  // delays: blocks then read plane l_hi over one time. A smallest delay, or a
+  // record shorter than its offsets, would make most of them windows that no
+  // output of the block lies in: there T0 = 0 is each block's own first window
+  // (Nf=1024, Nt=1024, Nd=64, smallest delay 100000: 32481 workgroups of the last
+  // pass, now 1568, and the adjoint 72 us, now 17 us; register gathers 19 us).
+  for (const Block &b : blocks) ps.extra = std::max(ps.extra, b.head[5]);
+  const bool own_start = to_input || ps.extra > nt;
+  ps.extra = 0;
+  for (Block &b : blocks) {
+    if (const int32_t first = own_start ? b.head[6] / ps.tile * ps.tile : 0) {
+      if (first > 1 << 28) return "offsets too large";
+      const int32_t *mids = s.block_mids.data() + ps.mid_offset + b.head[0];
+      for (int32_t x = mids[0]; x < mids[b.head[1]]; ++x) s.block_leaves1[ps.leaf_offset + x].shift4 += 4 * first;
+      for (int32_t x = 0; x < b.head[3]; ++x) s.block_outs[ps.out_offset + b.head[2] + x].beta -= first;
+      b.head[4] += first;
+      b.head[5] -= first;
+      b.head[6] -= first;
+    }
+    ps.extra = std::max(ps.extra, b.head[5]);
+    s.block_heads.insert(s.block_heads.end(), b.head.begin(), b.head.end());
+  }
+  ps.nblocks = static_cast<int>(blocks.size());
+  if (ps.extra > 2 * nt + 4 * ps.pitch) return "offsets of a block spread past its records";
   if (s.block_leaves1.size() > static_cast<size_t>(INT32_MAX) || s.block_leaves2.size() > static_cast<size_t>(INT32_MAX))
     return "adjoint schedule too large";
   for (int64_t x = ps.leaf_offset; x < ps.leaf_offset + ps.leaf1_count; ++x) {

@@ -226,16 +226,17 @@ struct AdjPass {
 // The window is one of plane l_hi: a range whose leaves have shifts lag, lag + 1,
 // ... holds plane m from T0 - lag on, and an output row reading that at shifts
 // beta0, beta0 + 1, ... gets its samples from T0 - beta on, beta = lag + beta0.
-// Each output row is tiled with an offset of its own, and `extra` (the largest
-// beta) more samples of windows cover every row's end. Sub-bands at large
-// shifts thus read the samples their neighbours read at the same time (with a
-// common window of plane m a pass fetched each 2.7 times). Sub-bands without
-// channels have no rows here: nothing reads them.
+// Each output row is tiled with an offset of its own, and `extra` more samples
+// of windows (the largest beta) cover every row's end. Sub-bands at large shifts
+// thus read the samples their neighbours read at the same time (with a common
+// window of plane m a pass fetched each 2.7 times). A block whose betas are all
+// large may count T0, and with it shifts and betas, from a time of its own.
+// Sub-bands without channels have no rows here: nothing reads them.
 //
 // Per block: [0] first row of plane m (in block_mids), [1] their number, [2]
 // first output (in block_outs), [3] their number, [4] largest shift of its
-// stage-1 leaves, [5] largest beta, [6] its first row of plane l_hi (the order
-// of the blocks).
+// stage-1 leaves, [5] largest beta, [6] smallest beta.
+// Blocks are ordered by their first row of plane l_hi.
 constexpr int kAdjBlockHeader = 8;
 constexpr int kAdjBlockRows = 36;  // most LDS rows of a block (72 KiB of windows of 512 samples, two workgroups per CU)
 
