@@ -107,7 +107,7 @@ __global__ __launch_bounds__(adj_threads(Q), 8) void adjoint_block_kernel(const 
   const int nt = bs.nt;
   const int t0 = bs.tile * a.tile;
   const Const<int32_t> head = as_const<int32_t>(a.heads) + static_cast<int64_t>(block) * kAdjBlockHeader;
-  if (t0 >= nt + head[5] || t0 + a.tile <= head[6]) return;  // past the end or before the start of every output row
+  if (t0 >= nt + head[5]) return;  // past the end of every output row
   const Const<int32_t> mids = as_const<int32_t>(a.mids) + head[0];
   const Const<Int2> leaves1 = as_const<Int2>(a.leaves1);
   const Const<Int2> places1 = as_const<Int2>(a.places1);

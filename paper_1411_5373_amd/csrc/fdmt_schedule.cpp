@@ -1110,14 +1110,14 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
   ps.leaves = ps.leaf1_count;
   ps.tile = (ps.pitch - spread) / align * align;
   if (ps.tile < 128 || spread > 128) return "block shifts spread too far";
-  // T0 = 0 is the same time in every block where the offsets are those of the
-  // delays: blocks then read plane l_hi over one time. A smallest delay, or a
-  // record shorter than its offsets, would make most of them windows that no
-  // output of the block lies in: there T0 = 0 is each block's own first window
+  // T0 = 0 is the same time in every block where the record is much longer than
+  // the offsets: blocks then read plane l_hi over one time. A smallest delay, or a
+  // short record, would make many of them windows that no output of the block
+  // lies in: there T0 = 0 is each block's own first window
   // (Nf=1024, Nt=1024, Nd=64, smallest delay 100000: 32481 workgroups of the last
   // pass, now 1568, and the adjoint 72 us, now 17 us; register gathers 19 us).
   for (const Block &b : blocks) ps.extra = std::max(ps.extra, b.head[5]);
-  const bool own_start = to_input || ps.extra > nt;
+  const bool own_start = to_input || 4 * static_cast<int64_t>(ps.extra) > nt;
   ps.extra = 0;
   for (Block &b : blocks) {
     if (const int32_t first = own_start ? b.head[6] / ps.tile * ps.tile : 0) {
