@@ -89,7 +89,7 @@ __device__ __forceinline__ void in_batches(int x0, int x1, F &&f) {
   if (rest == 1) f(x, std::integral_constant<int, 1>());
 }
 
-template <typename Tacc, int D1, int D2, int Q, bool RAGGED>
+template <typename Tacc, int D1, int D2, int Q, bool RAGGED, bool TURN>
 __global__ __launch_bounds__(adj_threads(Q), 8) void adjoint_block_kernel(const Tacc *__restrict__ src,
                                                                             Tacc *__restrict__ dst, AdjBlockArgs a,
                                                                             RaggedMap rg) {
@@ -101,7 +101,13 @@ __global__ __launch_bounds__(adj_threads(Q), 8) void adjoint_block_kernel(const 
   extern __shared__ __align__(16) unsigned char lds_raw[];
   Tacc *area = reinterpret_cast<Tacc *>(lds_raw);
   const int wave = uniform(threadIdx.x / 64), lane = threadIdx.x % 64;
-  const int block = xcd_local_order(blockIdx.x, a.nblocks);
+  int place = blockIdx.x;
+  if constexpr (TURN) {
+    const int even = a.nblocks & -a.nblocks, mask = (even < 8 ? even : 8) - 1;  // even: largest power of two in it
+    const int slot = place + static_cast<int>((blockIdx.y + gridDim.y * blockIdx.z) >> 4);
+    place = (place & ~mask) | (slot & mask);
+  }
+  const int block = xcd_local_order(place, a.nblocks);
   BeamSpan bs = beam_span<RAGGED>(rg, a.nt, a.src_stride, a.src_bstride, a.dst_stride, a.dst_bstride);
   if (!RAGGED && rg.reverse) bs.tile = static_cast<int>(gridDim.y) - 1 - bs.tile;
   const int nt = bs.nt;
@@ -212,34 +218,49 @@ size_t adjoint_block_lds_bytes(const AdjPass &ps) {
 template <typename Tacc>
 hipError_t launch_adjoint_block(const AdjBlockLaunch &g, const Tacc *src, Tacc *dst) {
   const AdjPass &ps = *g.pass;
+  // Blocks are unequal work, and a few of them whose number shares a factor with
+  // the 8 XCDs would run on the same XCDs in every tile: they change places every
+  // 16 tiles (64 beams of Nf=100, Nt=700, Nd=100 87 -> 55 us, 200 of Nf=50,
+  // Nt=1000, Nd=100 145 -> 127 us, Nf=64, Nt=100000, Nd=200 174 -> 149 us). With
+  // more blocks an XCD has several, and handing them on gained nothing or cost
+  // up to 8%; the test for it in the code cost 1% of short windows.
+  const bool turn = ps.nblocks <= 32 && ps.nblocks % 2 == 0 && g.grid.y * g.grid.z >= 128;
   AdjBlockArgs a{g.leaves1, g.places1, g.mids, g.outs, g.leaves2, g.heads, g.nt, ps.nblocks, ps.tile, g.streaming,
                  g.src_stride, g.src_bstride, g.dst_stride, g.dst_bstride};
   const size_t lds = adjoint_block_lds_bytes(ps);
+#define FDMT_ADJ_LAUNCH(A, B, QQ, R, T)                                                                           \
+  hipLaunchKernelGGL((adjoint_block_kernel<Tacc, A, B, QQ, R, T>), g.grid, dim3(adj_threads(QQ)), lds, g.stream,  \
+                     src, dst, a, g.rg)
 #define FDMT_ADJ_BLOCK(A, B, QQ)                                                                                  \
   if (ps.k1 == A && ps.depth2 == B && ps.pitch == 256 * QQ) {                                                     \
-    if (g.ragged)                                                                                                 \
-      hipLaunchKernelGGL((adjoint_block_kernel<Tacc, A, B, QQ, true>), g.grid, dim3(adj_threads(QQ)), lds,         \
-                         g.stream, src, dst, a, g.rg);                                                            \
+    if (g.ragged && turn)                                                                                         \
+      FDMT_ADJ_LAUNCH(A, B, QQ, true, true);                                                                      \
+    else if (g.ragged)                                                                                            \
+      FDMT_ADJ_LAUNCH(A, B, QQ, true, false);                                                                     \
+    else if (turn)                                                                                                \
+      FDMT_ADJ_LAUNCH(A, B, QQ, false, true);                                                                     \
     else                                                                                                          \
-      hipLaunchKernelGGL((adjoint_block_kernel<Tacc, A, B, QQ, false>), g.grid, dim3(adj_threads(QQ)), lds,        \
-                         g.stream, src, dst, a, g.rg);                                                            \
+      FDMT_ADJ_LAUNCH(A, B, QQ, false, false);                                                                    \
     return hipGetLastError();                                                                                     \
   }
 #define FDMT_ADJ_BLOCKS(F) F(1, 1, 1) F(1, 2, 1) F(2, 1, 1) F(2, 2, 1) F(2, 3, 1) F(1, 1, 2) F(1, 2, 2) F(2, 1, 2) F(2, 2, 2) F(2, 3, 2)
   FDMT_ADJ_BLOCKS(FDMT_ADJ_BLOCK)
 #undef FDMT_ADJ_BLOCK
+#undef FDMT_ADJ_LAUNCH
   return hipErrorInvalidValue;
 }
 
 hipError_t prepare_adjoint_blocks() {
   const int lds = kAdjBlockRows * 512 * 4 + 512;
+#define FDMT_ADJ_KERNEL(...) reinterpret_cast<const void *>(&adjoint_block_kernel<__VA_ARGS__>),
 #define FDMT_ADJ_FN(A, B, QQ)                                                                                     \
-  reinterpret_cast<const void *>(&adjoint_block_kernel<float, A, B, QQ, false>),                                  \
-      reinterpret_cast<const void *>(&adjoint_block_kernel<float, A, B, QQ, true>),                               \
-      reinterpret_cast<const void *>(&adjoint_block_kernel<int32_t, A, B, QQ, false>),                            \
-      reinterpret_cast<const void *>(&adjoint_block_kernel<int32_t, A, B, QQ, true>),
+  FDMT_ADJ_KERNEL(float, A, B, QQ, false, false) FDMT_ADJ_KERNEL(float, A, B, QQ, false, true)                    \
+  FDMT_ADJ_KERNEL(float, A, B, QQ, true, false) FDMT_ADJ_KERNEL(float, A, B, QQ, true, true)                      \
+  FDMT_ADJ_KERNEL(int32_t, A, B, QQ, false, false) FDMT_ADJ_KERNEL(int32_t, A, B, QQ, false, true)                \
+  FDMT_ADJ_KERNEL(int32_t, A, B, QQ, true, false) FDMT_ADJ_KERNEL(int32_t, A, B, QQ, true, true)
   const void *fns[] = {FDMT_ADJ_BLOCKS(FDMT_ADJ_FN)};
 #undef FDMT_ADJ_FN
+#undef FDMT_ADJ_KERNEL
 #undef FDMT_ADJ_BLOCKS
   for (const void *f : fns) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);

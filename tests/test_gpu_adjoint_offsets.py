@@ -37,3 +37,15 @@ def test_ragged(nf, nd, d_min, nt):
         if n:
             q = F.Plan(nf, n, nd, 1.2, 1.6, d_min=d_min, unfused=True)
             assert torch.equal(xb, q.adjoint(gb)), n
+
+
+@pytest.mark.parametrize("nf,nt,nd,batch", [(100, 700, 100, 40), (50, 1000, 100, 30), (64, 20000, 200, 3),
+                                            (16, 1000, 100, 50), (128, 1000, 128, 33), (8, 3001, 30, 20)])
+def test_blocks_that_change_places(nf, nt, nd, batch):
+    """2 to 32 blocks, an even number, over more than 16 tiles and beams."""
+    _check(nf, nt, nd, batch=batch)
+    lengths = [nt - 17 * b for b in range(batch) if nt > 17 * b]
+    r = F.RaggedPlan(F.Plan(nf, nt, nd, 1.2, 1.6), lengths)
+    g = _grad((nd * sum(lengths),), torch.float32, 3)
+    for n, gb, xb in list(zip(lengths, r.unpack(g, nd), r.unpack(r.adjoint(g), nf)))[::7]:
+        assert torch.equal(xb, F.Plan(nf, n, nd, 1.2, 1.6, unfused=True).adjoint(gb)), n
