@@ -457,10 +457,11 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
       } else {
         const int64_t eb = i > 0 && p.narrow[i - 1] ? 2 : 4;
         p.block_places.resize(p.fwd.terms.size());
-        for (int64_t j = ps.term_offset; j < ps.term_offset + ps.term_count; ++j) {
-          const fdmt::Term x = p.fwd.terms[j];
-          place((x.row * p.ntp - x.shift) * eb, p.block_places[j].row, p.block_places[j].shift);
-        }
+        for (const fdmt::Pass *form : {&ps, static_cast<const fdmt::Pass *>(&p.fwd.many[i])})
+          for (int64_t j = form->term_offset; j < form->term_offset + form->term_count; ++j) {
+            const fdmt::Term x = p.fwd.terms[j];
+            place((x.row * p.ntp - x.shift) * eb, p.block_places[j].row, p.block_places[j].shift);
+          }
       }
     }
   } catch (const std::bad_alloc &) {

@@ -747,7 +747,9 @@ hipError_t run_forward_step(const Plan &p, const Step &st, const void *in, void 
         return hipSuccess;
       });
     case Step::Fused: {
-      const Pass &ps = p.fwd.passes[st.index];
+      const bool many = rb == nullptr && st.index < static_cast<int>(p.fwd.many.size()) &&
+                        p.fwd.many[st.index].records > 0 && batch >= p.fwd.many[st.index].records;
+      const Pass &ps = many ? p.fwd.many[st.index] : p.fwd.passes[st.index];
       if (ps.kind == PassKind::Staged) {
         if (rb != nullptr) return hipErrorInvalidValue;
         StagedArgs a{};

@@ -624,8 +624,9 @@ std::string block_offsets(const Tables &t, int l, int k, const Node *tops, int n
   return "";
 }
 
-std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, int k, bool from_input, bool bytes) {
-  Pass ps;
+// `many`: whole blocks, for batches of so many records that they fill the GPU.
+std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, int k, bool from_input, bool bytes,
+                             bool many, Pass &ps) {
   ps.kind = PassKind::Block;
   ps.from_input = from_input;
   ps.l0 = l0;
@@ -649,7 +650,11 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
     for (int32_t r : t.rows[ps.l1]) n += row_parts(r, max_rows, t.slots >> ps.l1);
     return n;
   };
-  while (max_rows > 4 && count_blocks() * tiles < 256) max_rows /= 2;
+  if (!many)
+    while (max_rows > 4 && count_blocks() * tiles < 256) {
+      max_rows /= 2;
+      ps.few = true;
+    }
   // Packed 16-bit sums: exact while 255 (2^l1 + rows - 1), the largest sum of
   // uint8 samples, fits, and worth it once the wider tiles fill the GPU.
   int widest = 0;
@@ -764,7 +769,6 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
   if ((ps.rows_a + ps.rows_b + 1) * kBlockPitch * 4 > 64 * 1024) return "block rows do not fit LDS";
   ps.nblocks = static_cast<int>(blocks.size());
   ps.term_count = static_cast<int64_t>(from_input ? s.iterms.size() : s.terms.size()) - ps.term_offset;
-  s.passes.push_back(ps);
   return "";
 }
 
@@ -781,8 +785,23 @@ std::string build_block_schedule(Schedule &s, const Tables &t, int64_t nt, bool 
   int l0 = 0;
   for (int i = 0; i < passes; ++i) {
     const int k = (L - l0 + passes - i - 1) / (passes - i);
-    const std::string err = build_block_pass(s, t, nt, l0, k, i == 0 && !s.init_separate, bytes);
+    const bool from_input = i == 0 && !s.init_separate;
+    Pass one, many;
+    const std::string err = build_block_pass(s, t, nt, l0, k, from_input, bytes, false, one);
     if (!err.empty()) return err;
+    // Blocks of 4 rows load two to three times the terms per output of blocks of 16
+    // or 18: a batch takes whole ones where they come to two workgroups per CU (256
+    // records of Nf=64, Nt=1024, Nd=64 FP32 159 -> 77 us, 64 of Nf=256, Nt=500,
+    // Nd=256 121 -> 90 us). With fewer the smaller blocks can be the faster ones (8 of
+    // the latter 22.7 us, 23.4 us with whole ones; 4 of the former 7.8 and 10.2 us).
+    if (one.few && build_block_pass(s, t, nt, l0, k, from_input, bytes, true, many).empty()) {
+      const int64_t each = many.nblocks * ((nt + many.tile - 1) / many.tile);
+      many.records = std::max<int64_t>(2, (511 + each) / each);
+    } else {
+      many = Pass();
+    }
+    s.passes.push_back(one);
+    s.many.push_back(many);
     l0 += k;
   }
   if (search) {

@@ -92,6 +92,8 @@ struct Pass {
   int tiles_per_wg = 1;        // Block: consecutive time tiles of a workgroup
   int64_t term_count = 0;      // Block: stage-1 terms of the pass
   int64_t offs_offset = 0;     // Block: first LDS offset in Schedule::block_offs (heads: head_offset)
+  bool few = false;            // Block: rows per block cut down so that one record fills the GPU
+  int64_t records = 0;         // Block: records from which a batch takes this form (see Schedule::many)
 };
 
 // Block passes. A work item is a range of consecutive rows of one sub-band of
@@ -159,6 +161,8 @@ struct Schedule {
                                 // b = LDS of the staged input row, c = last partial-sum row,
                                 // d = partial-sum row stride, e = width, f = input columns ahead
   std::vector<int32_t> sheads;  // staged passes: kStagedHeader per block
+  std::vector<Pass> many;       // block passes: the same for batches of many[i].records records or more,
+                                // with whole blocks where one record needs smaller ones (0: the same form)
   std::vector<int32_t> block_offs;   // block passes: LDS offsets of stage 2 and 3 terms
   std::vector<int32_t> block_heads;  // block passes: kBlockHeader per block
 };
