@@ -666,7 +666,10 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
   ps.k1 = sp.k1;
   ps.k2 = sp.k2;
   ps.k3 = sp.k3;
-  // A node's width with a tile of 0 samples is the spread of its shifts.
+  // The trees of the rows in LDS, area A's first (level 0; level i's nodes start at
+  // 2^(kl+1) - 2^(kl+1-i)). A node's width with a tile of 0 samples is the spread of
+  // its shifts.
+  const int kl = k - ps.k1;
   struct Range {
     int sub, r0, nr;
     Tree tree;
@@ -681,12 +684,10 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
     for (int b = 0; b < nb; ++b) {
       const int r0 = static_cast<int>(static_cast<int64_t>(n) * b / nb);
       const int r1 = static_cast<int>(static_cast<int64_t>(n) * (b + 1) / nb);
-      blocks.push_back({sub, r0, r1 - r0, build_tree(t, false, l0, ps.l1, sub, r0, r1 - r0, 0)});
+      blocks.push_back({sub, r0, r1 - r0, build_tree(t, false, l0 + ps.k1, ps.l1, sub, r0, r1 - r0, 0)});
       const Tree &tr = blocks.back().tree;
-      // nodes level by level, leaves first: the nodes of level i start at 2^(k+1) - 2^(k+1-i)
-      const size_t a = (2u << k) - (2u << (k - ps.k1));
-      for (size_t j = a; j < tr.nodes.size(); ++j) spread = std::max(spread, tr.nodes[j].width);
-      for (size_t j = a; j < a + (1u << (k - ps.k1)); ++j) lds_rows += tr.nodes[j].nrows;
+      for (const Node &x : tr.nodes) spread = std::max(spread, x.width);
+      for (int j = 0; j < 1 << kl; ++j) lds_rows += tr.nodes[j].nrows;
     }
   }
   const int lead = (from_input ? kBlockLead : 0) * (ps.packed ? 2 : 1);
@@ -697,10 +698,14 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
   Term cur[8];
   const int terms1 = 1 << ps.k1;
   std::vector<int> base_a, base_b;
-  if (from_input) s.iterms.reserve(s.iterms.size() + lds_rows * terms1);
-  else s.terms.reserve(s.terms.size() + lds_rows * terms1);
+  ps.term_count = static_cast<int64_t>(lds_rows * terms1);
+  if (from_input) s.iterms.resize(ps.term_offset + ps.term_count);
+  else s.terms.resize(ps.term_offset + ps.term_count);
+  InTerm *iterm = s.iterms.data() + ps.term_offset;  // used by a pass from the input
+  Term *term = s.terms.data() + ps.term_offset;      // used by one from a plane
+  int32_t terms = 0;
   for (const Range &b : blocks) {
-    const auto level = [&](int i) { return b.tree.nodes.data() + ((2 << k) - (2 << (k - i))); };
+    const auto level = [&](int i) { return b.tree.nodes.data() + ((2 << kl) - (2 << (kl - i))); };
     const auto bases = [](const Node *n, int count, std::vector<int> &base) {
       int rows = 0;
       base.resize(count);
@@ -711,10 +716,10 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
       return rows;
     };
     int32_t head[kBlockHeader] = {};
-    head[0] = static_cast<int32_t>((from_input ? s.iterms.size() : s.terms.size()) - ps.term_offset);
+    head[0] = terms;
     // stage 1: the rows of area A, each term's shift counted from the row's column 0
-    const Node *na = level(ps.k1);
-    const int count_a = 1 << (k - ps.k1);
+    const Node *na = level(0);
+    const int count_a = 1 << kl;
     const int rows_a = bases(na, count_a, base_a);
     int reach = 0;
     for (int j = 0; j < count_a; ++j) {
@@ -728,12 +733,13 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
             const int ch = channel_of[x.row];
             const int d = x.row - t.leaf_off[ch];
             // a position without a channel: past the start of every record, so zero
-            s.iterms.push_back(ch < t.nf ? InTerm{ch, shift + t.pre[ch], d, 0} : InTerm{0, kNoChannelPre, 0, 0});
-            reach = std::max(reach, s.iterms.back().shift);
+            const InTerm y = ch < t.nf ? InTerm{ch, shift + t.pre[ch], d, 0} : InTerm{0, kNoChannelPre, 0, 0};
+            iterm[terms++] = y;
+            reach = std::max(reach, y.shift);
             ps.staged_rows += d + 1;
             ps.max_chain = std::max(ps.max_chain, d);
           } else {
-            s.terms.push_back(Term{x.row, shift});
+            term[terms++] = Term{x.row, shift};
             reach = std::max(reach, shift);
             ++ps.staged_rows;
           }
@@ -748,7 +754,7 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
     int rows_b = 0;
     std::string err;
     if (ps.k2 > 0) {
-      const Node *nb = level(ps.k1 + ps.k2);
+      const Node *nb = level(ps.k2);
       const int count_b = 1 << ps.k3;
       rows_b = bases(nb, count_b, base_b);
       err = block_offsets(t, l0 + ps.k1 + ps.k2, ps.k2, nb, count_b, na, base_a, lead, ps, s.block_offs);
@@ -758,7 +764,7 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
     }
     head[3] = rows_b;
     head[4] = static_cast<int32_t>(s.block_offs.size() - ps.offs_offset);
-    err = block_offsets(t, ps.l1, ps.k3, level(k), 1, below, *base, ps.k2 > 0 ? 0 : lead, ps, s.block_offs);
+    err = block_offsets(t, ps.l1, ps.k3, level(kl), 1, below, *base, ps.k2 > 0 ? 0 : lead, ps, s.block_offs);
     if (!err.empty()) return err;
     head[5] = b.nr;
     head[6] = static_cast<int32_t>(t.row_off[ps.l1][b.sub] + b.r0);
@@ -768,7 +774,6 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
   }
   if ((ps.rows_a + ps.rows_b + 1) * kBlockPitch * 4 > 64 * 1024) return "block rows do not fit LDS";
   ps.nblocks = static_cast<int>(blocks.size());
-  ps.term_count = static_cast<int64_t>(from_input ? s.iterms.size() : s.terms.size()) - ps.term_offset;
   return "";
 }
 
@@ -1023,14 +1028,13 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
   Block block{};
   int block_rows = 0, spread = 0;
   std::vector<AdjLeaf> leaves;
-  std::vector<AdjBlockLeaf> range;  // the range's stage-1 leaves
-  std::vector<int32_t> starts, betas;
+  std::vector<int32_t> betas;
   s.block_leaves1.reserve(s.block_leaves1.size() + static_cast<size_t>(rows) * 6);
   s.block_leaves2.reserve(s.block_leaves2.size() + pool.size());
   s.block_outs.reserve(s.block_outs.size() + outs.size());
   const auto flush = [&]() {
     if (block_rows == 0) return;
-    block.head[1] = static_cast<int32_t>(s.block_mids.size() - ps.mid_offset) - block.head[0];
+    block.head[1] = block_rows;
     block.head[3] = static_cast<int32_t>(s.block_outs.size() - ps.out_offset) - block.head[2];
     blocks.push_back(block);
     ps.rows_mid = std::max(ps.rows_mid, block_rows);
@@ -1041,15 +1045,15 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
     // The range's smallest stage-1 shift moves its window instead of its
     // leaves: every range then reads plane l_hi over one and the same time.
     int32_t lag = INT32_MAX;
-    range.clear();
-    starts.clear();
+    const int32_t mid = static_cast<int32_t>(s.block_mids.size() - ps.mid_offset);
+    const size_t leaf = s.block_leaves1.size();
     for (int32_t r = lo; r <= hi; ++r) {
       leaves.clear();
       AdjWalker w{t, l_hi, leaves};
       w.visit(m, r, 0, 0, 0);
-      starts.push_back(static_cast<int32_t>(range.size()));
+      s.block_mids.push_back(static_cast<int32_t>(s.block_leaves1.size() - ps.leaf_offset));
       for (const AdjLeaf &e : leaves) {
-        range.push_back(AdjBlockLeaf{e.row, 4 * e.shift + e.branch});
+        s.block_leaves1.push_back(AdjBlockLeaf{e.row, 4 * e.shift + e.branch});
         lag = std::min(lag, e.shift);
       }
     }
@@ -1073,17 +1077,14 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
       flush();
     if (block_rows == 0) {
       block = Block{};
-      block.head[0] = static_cast<int32_t>(s.block_mids.size() - ps.mid_offset);
+      block.head[0] = mid;
       block.head[2] = static_cast<int32_t>(s.block_outs.size() - ps.out_offset);
       block.head[6] = INT32_MAX;
-      block.row = range[0].row;
+      block.row = s.block_leaves1[leaf].row;
     }
-    const int32_t base = static_cast<int32_t>(s.block_leaves1.size() - ps.leaf_offset);
-    for (int32_t x : starts) s.block_mids.push_back(base + x);
-    for (AdjBlockLeaf e : range) {
-      e.shift4 -= 4 * lag;
-      block.head[4] = std::max(block.head[4], e.shift4 >> 2);
-      s.block_leaves1.push_back(e);
+    for (size_t x = leaf; x < s.block_leaves1.size(); ++x) {
+      s.block_leaves1[x].shift4 -= 4 * lag;
+      block.head[4] = std::max(block.head[4], s.block_leaves1[x].shift4 >> 2);
     }
     block.head[5] = std::max(block.head[5], far);
     block.head[6] = std::min(block.head[6], near);
