@@ -55,8 +55,12 @@ double merge_coefficient(double f0, double f1, double f2, double gamma) {
   return num / den;
 }
 
-// Nearest integer, ties upward; x >= 0 here.
-int32_t round_half_up(double x) { return static_cast<int32_t>(std::floor(x + 0.5)); }
+// Nearest integer, ties upward: floor(x + 0.5) without a library call.
+int32_t round_half_up(double x) {
+  const double y = x + 0.5;
+  const int32_t i = static_cast<int32_t>(y);
+  return i - (y < i ? 1 : 0);
+}
 
 } // namespace
 
@@ -96,13 +100,25 @@ std::string build_tables(Tables &t, int nf, int nd, double f_min, double f_max, 
 
   // Top-down: split every sub-band of iteration l, which fixes the row counts
   // of iteration l - 1.
-  std::vector<std::vector<std::vector<int32_t>>> lo_of(levels + 1), hi_of(levels + 1), s_of(levels + 1);
+  t.row_off.assign(levels + 1, {});
+  t.total.assign(levels + 1, 0);
+  const auto offsets = [&](int l) {
+    int64_t acc = 0;
+    t.row_off[l].resize(t.rows[l].size());
+    for (size_t j = 0; j < t.rows[l].size(); ++j) {
+      t.row_off[l][j] = acc;
+      acc += t.rows[l][j];
+    }
+    t.total[l] = acc;
+  };
   for (int l = levels; l >= 1; --l) {
     const int nsub = slots >> l;
     t.rows[l - 1].assign(2 * nsub, 0);
-    lo_of[l].resize(nsub);
-    hi_of[l].resize(nsub);
-    s_of[l].resize(nsub);
+    offsets(l);
+    if (t.total[l] > INT32_MAX) return "plane too tall";
+    t.d_lo[l].resize(t.total[l]);
+    t.d_hi[l].resize(t.total[l]);
+    t.shift[l].resize(t.total[l]);
     for (int j = 0; j < nsub; ++j) {
       const int64_t first = static_cast<int64_t>(j) << l, mid = static_cast<int64_t>(2 * j + 1) << (l - 1);
       const int64_t end = std::min<int64_t>(static_cast<int64_t>(j + 1) << l, nf);  // past its last channel
@@ -118,12 +134,9 @@ std::string build_tables(Tables &t, int nf, int nd, double f_min, double f_max, 
         c_hi = merge_coefficient(edge[first], edge[mid], edge[end - 1], gamma);
       }
       const int32_t n = t.rows[l][j];
-      auto &lo = lo_of[l][j];
-      auto &hi = hi_of[l][j];
-      auto &sh = s_of[l][j];
-      lo.resize(n);
-      hi.resize(n);
-      sh.resize(n);
+      int32_t *lo = t.d_lo[l].data() + t.row_off[l][j];
+      int32_t *hi = t.d_hi[l].data() + t.row_off[l][j];
+      int32_t *sh = t.shift[l].data() + t.row_off[l][j];
       for (int32_t dt = 0; dt < n; ++dt) {
         const int32_t d = round_half_up(static_cast<double>(dt) * c_lo);
         const int32_t sv = round_half_up(static_cast<double>(dt) * c_hi);
@@ -137,19 +150,8 @@ std::string build_tables(Tables &t, int nf, int nd, double f_min, double f_max, 
     }
   }
 
-  // Row offsets of every plane.
-  t.row_off.assign(levels + 1, {});
-  t.total.assign(levels + 1, 0);
-  for (int l = 0; l <= levels; ++l) {
-    int64_t acc = 0;
-    t.row_off[l].resize(t.rows[l].size());
-    for (size_t j = 0; j < t.rows[l].size(); ++j) {
-      t.row_off[l][j] = acc;
-      acc += t.rows[l][j];
-    }
-    t.total[l] = acc;
-    if (acc > INT32_MAX) return "plane too tall";
-  }
+  offsets(0);
+  if (t.total[0] > INT32_MAX) return "plane too tall";
 
   // Flat per-row tables.
   t.merge.assign(levels + 1, {});
@@ -158,9 +160,6 @@ std::string build_tables(Tables &t, int nf, int nd, double f_min, double f_max, 
     const int nsub = slots >> l;
     auto &m = t.merge[l];
     m.resize(t.total[l]);
-    t.d_lo[l].resize(t.total[l]);
-    t.d_hi[l].resize(t.total[l]);
-    t.shift[l].resize(t.total[l]);
     auto &a = t.adj[l];
     a.assign(t.total[l - 1], AdjRow{0, 0, 0, 0});
     for (int j = 0; j < nsub; ++j) {
@@ -168,12 +167,9 @@ std::string build_tables(Tables &t, int nf, int nd, double f_min, double f_max, 
       const int64_t lo_base = t.row_off[l - 1][2 * j];
       const int64_t hi_base = t.row_off[l - 1][2 * j + 1];
       for (int32_t dt = 0; dt < t.rows[l][j]; ++dt) {
-        const int32_t dl = lo_of[l][j][dt], dh = hi_of[l][j][dt], sv = s_of[l][j][dt];
         const int64_t r = base + dt;
+        const int32_t dl = t.d_lo[l][r], dh = t.d_hi[l][r], sv = t.shift[l][r];
         m[r] = MergeRow{static_cast<int32_t>(lo_base + dl), static_cast<int32_t>(hi_base + dh), sv, j};
-        t.d_lo[l][r] = dl;
-        t.d_hi[l][r] = dh;
-        t.shift[l][r] = sv;
         // Inverse maps: the parents of a child row are consecutive because
         // both d_lo and d_hi are non-decreasing in dt.
         AdjRow &al = a[lo_base + dl];
