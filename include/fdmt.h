@@ -297,7 +297,8 @@ fdmt_status_t fdmt_plan_destroy(fdmt_plan_t p);
  * step of a transform is one launch over all beams (a further launch per
  * 65535 time tiles of that step), so the beam count does not multiply the
  * launch count. Beam b has nt[b] samples (0 allowed); the delay tables and
- * schedule are the plan's, whose own Nt only shapes its schedule. Results per beam are
+ * schedule are the plan's, whose own Nt only shapes its schedule (block passes
+ * take the form that the batch's samples fill the GPU with). Results per beam are
  * bit-identical to fdmt_forward()/fdmt_adjoint() of a plan with Nt = nt[b].
  *
  * Packed layout (dense, time fastest): beam b's [rows][nt[b]] block starts at

@@ -743,12 +743,13 @@ fdmt_status_t fdmt_ragged_plan(fdmt_ragged_t *out, fdmt_plan_t p, int32_t nbeams
   if (!nt) return fail(FDMT_E_INVALID, "nt is NULL");
   if (nbeams < 1) return fail(FDMT_E_INVALID, "nbeams must be at least 1");
   const fdmt::Plan &P = p->plan;
-  int64_t sum = 0, sump = 0;
+  int64_t sum = 0, sump = 0, tiled = 0;
   for (int32_t b = 0; b < nbeams; ++b) {
     if (nt[b] < 0 || nt[b] > INT32_MAX)
       return fail(FDMT_E_INVALID, "beam " + std::to_string(b) + ": Nt must be in [0, 2^31 - 1]");
     sum += nt[b];
     sump += fdmt::round_up(nt[b], fdmt::kRowAlign);
+    tiled += fdmt::round_up(nt[b], fdmt::kBlockTile);
     if (sump > INT32_MAX) return fail(FDMT_E_UNSUPPORTED, "total samples of the batch exceed 2^31 - 1");
   }
   // Tile widths of every step of both transforms.
@@ -756,7 +757,7 @@ fdmt_status_t fdmt_ragged_plan(fdmt_ragged_t *out, fdmt_plan_t p, int32_t nbeams
   for (int adj = 0; adj < 2; ++adj) {
     const int n = static_cast<int>(adj ? P.adj_steps.size() : P.fwd_steps.size());
     for (int i = 0; i < n; ++i) {
-      const int w = fdmt::step_tile(P, adj != 0, i);
+      const int w = fdmt::step_tile(P, adj != 0, i, tiled);
       if (w <= 0) return fail(FDMT_E_UNSUPPORTED, "the plan's staged-gather passes have no ragged form");
       const std::pair<int, int32_t> key(w, fdmt::step_extra(P, adj != 0, i));
       if (std::find(widths.begin(), widths.end(), key) == widths.end()) widths.push_back(key);
@@ -828,6 +829,7 @@ fdmt_status_t fdmt_ragged_plan(fdmt_ragged_t *out, fdmt_plan_t p, int32_t nbeams
   h->rb.nbeams = nbeams;
   h->rb.sum_nt = sum;
   h->rb.sum_ntp = sump;
+  h->rb.tiled = tiled;
   h->rb.beam = reinterpret_cast<const int4 *>(base);
   for (size_t m = 0; m < widths.size(); ++m)
     h->rb.maps.push_back({widths[m].first, widths[m].second, static_cast<int64_t>(maps[m].size()),
@@ -882,7 +884,7 @@ fdmt_status_t fdmt_ragged_info(fdmt_ragged_t r, int32_t *nbeams, int64_t *total_
     for (int adj = 0; adj < 2; ++adj) {
       const int k = static_cast<int>(adj ? P.adj_steps.size() : P.fwd_steps.size());
       for (int i = 0; i < k; ++i) {
-        const int w = fdmt::step_tile(P, adj != 0, i);
+        const int w = fdmt::step_tile(P, adj != 0, i, r->rb.tiled);
         for (const fdmt::RaggedBatch::Map &m : r->rb.maps)
           if (m.tile == w && m.extra == fdmt::step_extra(P, adj != 0, i)) n += static_cast<int32_t>((m.count + 65534) / 65535);
       }

@@ -116,7 +116,7 @@ struct BlockArgs {
   int32_t nt, nblocks, tile, rows_a;
   int32_t tiles_per_wg;  // consecutive time tiles of a workgroup
   int32_t streaming;  // output not read again by this call: non-temporal stores
-  int32_t turn;       // see xcd_turned_order()
+  int32_t turn;       // uniform: see xcd_turned_order(); ragged: blocks that change places, less 1
   int64_t src_stride, src_bstride, dst_stride, dst_bstride;
 };
 
@@ -185,8 +185,10 @@ __global__ __launch_bounds__(kBlockThreads, 8) void block_pass_kernel(const Tsrc
   Tacc *area_a = reinterpret_cast<Tacc *>(lds_raw);
   Tacc *area_b = area_a + a.rows_a * kBlockPitch;
   const int wave = uniform(threadIdx.x / 64), lane = threadIdx.x % 64;
-  const int block = FROM_INPUT && !RAGGED ? xcd_turned_order(blockIdx.x, a.nblocks, a.turn)
-                                          : xcd_local_order(blockIdx.x, a.nblocks);
+  int place = blockIdx.x;
+  if constexpr (RAGGED) place = (place & ~a.turn) | ((place + static_cast<int>(blockIdx.y >> 4)) & a.turn);
+  const int block = FROM_INPUT && !RAGGED ? xcd_turned_order(place, a.nblocks, a.turn)
+                                          : xcd_local_order(place, a.nblocks);
   BeamSpan bs = beam_span<RAGGED>(rg, a.nt, a.src_stride, a.src_bstride, a.dst_stride, a.dst_bstride);
   if (!RAGGED && rg.reverse) bs.tile = static_cast<int>(gridDim.y) - 1 - bs.tile;
   const int nt = bs.nt;
@@ -548,7 +550,13 @@ hipError_t launch_block(const BlockLaunch &g, const Tsrc *src, Tdst *dst) {
   // L2's overlap of neighbouring tiles (0.466, 0.450 ms). A pass from a plane
   // reads most of it again in the next tile and got slower (up to 8%, with the
   // test alone in its code 5%), packed and ragged passes gained nothing.
-  a.turn = FROM_INPUT && !ps.packed && ps.nblocks % 8 == 0 && ps.nblocks >= 64 && g.grid.y * g.grid.z >= 128 ? 4 : 0;
+  // Ragged batches of a few blocks whose number shares a factor with the 8 XCDs
+  // hand them on too: 500 beams of 30 to 800 samples, Nf=256, Nd=128 FP32 301 -> 258 us,
+  // 60 of 500 to 5000, Nf=1024, Nd=300 355 -> 317 us.
+  const int even = ps.nblocks & -ps.nblocks;  // largest power of two in it
+  if (g.ragged) a.turn = !ps.packed && ps.nblocks <= 32 ? (even < 8 ? even : 8) - 1 : 0;
+  else
+    a.turn = FROM_INPUT && !ps.packed && ps.nblocks % 8 == 0 && ps.nblocks >= 64 && g.grid.y * g.grid.z >= 128 ? 4 : 0;
   a.rows_a = ps.rows_a;
   a.streaming = g.streaming;
   a.src_stride = g.src_stride;

@@ -747,9 +747,7 @@ hipError_t run_forward_step(const Plan &p, const Step &st, const void *in, void 
         return hipSuccess;
       });
     case Step::Fused: {
-      const bool many = rb == nullptr && st.index < static_cast<int>(p.fwd.many.size()) &&
-                        p.fwd.many[st.index].records > 0 && batch >= p.fwd.many[st.index].records;
-      const Pass &ps = many ? p.fwd.many[st.index] : p.fwd.passes[st.index];
+      const Pass &ps = forward_pass(p, st.index, rb ? rb->tiled : batch * round_up(nt, kBlockTile));
       if (ps.kind == PassKind::Staged) {
         if (rb != nullptr) return hipErrorInvalidValue;
         StagedArgs a{};
@@ -1246,7 +1244,13 @@ int adjoint_threads(const Plan &p, int pass) {
   return p.adj.passes[pass].to_input && p.adjoint_last_threads ? p.adjoint_last_threads : p.adjoint_threads;
 }
 
-int step_tile(const Plan &p, bool adjoint, int i) {
+const Pass &forward_pass(const Plan &p, int i, int64_t samples) {
+  const std::vector<Pass> &many = p.fwd.many;
+  const bool whole = i < static_cast<int>(many.size()) && many[i].samples > 0 && samples >= many[i].samples;
+  return whole ? many[i] : p.fwd.passes[i];
+}
+
+int step_tile(const Plan &p, bool adjoint, int i, int64_t samples) {
   const Step &st = adjoint ? p.adj_steps[i] : p.fwd_steps[i];
   switch (st.kind) {
     case Step::PadIn:
@@ -1259,7 +1263,7 @@ int step_tile(const Plan &p, bool adjoint, int i) {
       return adjoint_wave_span(p.gather_vecs, p.adj.passes[st.index].lagged) *
              (adjoint_threads(p, st.index) / 64 / adjoint_rows(p, st.index));
     case Step::Fused: {
-      const Pass &ps = p.fwd.passes[st.index];
+      const Pass &ps = forward_pass(p, st.index, samples);
       if (ps.kind == PassKind::Staged) return 0;
       if (ps.kind == PassKind::Block) return ps.tile * ps.tiles_per_wg;
       return ps.gather ? 256 * forward_vecs(p, ps) * (forward_threads(p, ps) / 64 / forward_rows(p, ps))

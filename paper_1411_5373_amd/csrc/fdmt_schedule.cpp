@@ -800,8 +800,7 @@ std::string build_block_schedule(Schedule &s, const Tables &t, int64_t nt, bool 
     // Nd=256 121 -> 90 us). With fewer the smaller blocks can be the faster ones (8 of
     // the latter 22.7 us, 23.4 us with whole ones; 4 of the former 7.8 and 10.2 us).
     if (one.few && build_block_pass(s, t, nt, l0, k, from_input, bytes, true, many).empty()) {
-      const int64_t each = many.nblocks * ((nt + many.tile - 1) / many.tile);
-      many.records = std::max<int64_t>(2, (511 + each) / each);
+      many.samples = (511 + many.nblocks) / many.nblocks * static_cast<int64_t>(kBlockTile);
     } else {
       many = Pass();
     }

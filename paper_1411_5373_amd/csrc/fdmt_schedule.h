@@ -93,7 +93,8 @@ struct Pass {
   int64_t term_count = 0;      // Block: stage-1 terms of the pass
   int64_t offs_offset = 0;     // Block: first LDS offset in Schedule::block_offs (heads: head_offset)
   bool few = false;            // Block: rows per block cut down so that one record fills the GPU
-  int64_t records = 0;         // Block: records from which a batch takes this form (see Schedule::many)
+  int64_t samples = 0;         // Block: samples of a batch, each record in whole tiles of kBlockTile, from
+                               // which it takes this form (see Schedule::many)
 };
 
 // Block passes. A work item is a range of consecutive rows of one sub-band of
@@ -120,6 +121,7 @@ constexpr int kBlockTail = 4;
 // stage-2 offset, [3] rows of B, [4] first stage-3 offset, [5] output rows,
 // [6] first output row (plane l1), [7] largest shift of its stage-1 terms.
 constexpr int kBlockHeader = 8;
+constexpr int kBlockTile = 224;    // time tile where the shifts of a block spread as little as they mostly do
 constexpr int kBlockLevels = 6;    // most iterations of a block pass
 constexpr int kBlockMaxChain = kBlockLead;  // longest Option-1 chain a first pass from the input adds up itself
 
@@ -161,7 +163,7 @@ struct Schedule {
                                 // b = LDS of the staged input row, c = last partial-sum row,
                                 // d = partial-sum row stride, e = width, f = input columns ahead
   std::vector<int32_t> sheads;  // staged passes: kStagedHeader per block
-  std::vector<Pass> many;       // block passes: the same for batches of many[i].records records or more,
+  std::vector<Pass> many;       // block passes: the same for batches of many[i].samples samples or more,
                                 // with whole blocks where one record needs smaller ones (0: the same form)
   std::vector<int32_t> block_offs;   // block passes: LDS offsets of stage 2 and 3 terms
   std::vector<int32_t> block_heads;  // block passes: kBlockHeader per block

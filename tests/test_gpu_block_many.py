@@ -42,3 +42,18 @@ def test_step_by_step():
     for i in range(len(p.steps())):
         p.run_step(False, i, x, y, ws)
     assert torch.equal(y, q.forward(x))
+
+
+@pytest.mark.parametrize("form", ["f32", "u8"])
+def test_ragged(form):
+    """A ragged batch takes whole blocks by its samples, whatever the plan's Nt."""
+    import paper_1411_5373_amd as F
+    nf, nd = 100, 90
+    p, _ = _pair(nf, 300, nd, form)
+    for lengths in ([300, 0, 17], [224 + 3 * b for b in range(120)], [30000, 1, 449]):
+        r = F.RaggedPlan(p, lengths)
+        x = _input((nf * sum(lengths),), FORMS[form][0], 2)
+        y = r.unpack(r.forward(x), nd)
+        for n, xb, yb in list(zip(lengths, r.unpack(x, nf), y))[::11 if len(lengths) > 9 else 1]:
+            if n:
+                assert torch.equal(yb, _pair(nf, n, nd, form)[1].forward(xb)), n
