@@ -430,12 +430,13 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
   try {
     p.adj_places.resize(p.adj.block_leaves1.size());
     for (size_t i = 0; i < p.adj.passes.size(); ++i) {
-      const fdmt::AdjPass &ps = p.adj.passes[i];
-      for (int64_t j = ps.leaf_offset; ps.block && j < ps.leaf_offset + ps.leaf1_count; ++j) {
-        const fdmt::AdjBlockLeaf &x = p.adj.block_leaves1[j];
-        const int64_t at = (x.row * (i == 0 ? nt : p.ntp) + (x.shift4 >> 2)) * 4 + (x.shift4 & 3);
-        p.adj_places[j] = {static_cast<int32_t>(static_cast<uint32_t>(at)), static_cast<int32_t>(at >> 32)};
-      }
+      if (!p.adj.passes[i].block) continue;
+      for (const fdmt::AdjPass *ps : {&p.adj.passes[i], &p.adj.many[i]})
+        for (int64_t j = ps->leaf_offset; j < ps->leaf_offset + ps->leaf1_count; ++j) {
+          const fdmt::AdjBlockLeaf &x = p.adj.block_leaves1[j];
+          const int64_t at = (x.row * (i == 0 ? nt : p.ntp) + (x.shift4 >> 2)) * 4 + (x.shift4 & 3);
+          p.adj_places[j] = {static_cast<int32_t>(static_cast<uint32_t>(at)), static_cast<int32_t>(at >> 32)};
+        }
     }
     for (size_t i = 0; i < p.fwd.passes.size(); ++i) {
       const fdmt::Pass &ps = p.fwd.passes[i];
@@ -759,7 +760,7 @@ fdmt_status_t fdmt_ragged_plan(fdmt_ragged_t *out, fdmt_plan_t p, int32_t nbeams
     for (int i = 0; i < n; ++i) {
       const int w = fdmt::step_tile(P, adj != 0, i, tiled);
       if (w <= 0) return fail(FDMT_E_UNSUPPORTED, "the plan's staged-gather passes have no ragged form");
-      const std::pair<int, int32_t> key(w, fdmt::step_extra(P, adj != 0, i));
+      const std::pair<int, int32_t> key(w, fdmt::step_extra(P, adj != 0, i, tiled));
       if (std::find(widths.begin(), widths.end(), key) == widths.end()) widths.push_back(key);
     }
   }
@@ -886,7 +887,7 @@ fdmt_status_t fdmt_ragged_info(fdmt_ragged_t r, int32_t *nbeams, int64_t *total_
       for (int i = 0; i < k; ++i) {
         const int w = fdmt::step_tile(P, adj != 0, i, r->rb.tiled);
         for (const fdmt::RaggedBatch::Map &m : r->rb.maps)
-          if (m.tile == w && m.extra == fdmt::step_extra(P, adj != 0, i)) n += static_cast<int32_t>((m.count + 65534) / 65535);
+          if (m.tile == w && m.extra == fdmt::step_extra(P, adj != 0, i, r->rb.tiled)) n += static_cast<int32_t>((m.count + 65534) / 65535);
       }
     }
     *launches = n;

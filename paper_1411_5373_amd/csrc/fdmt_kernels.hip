@@ -942,7 +942,7 @@ hipError_t run_adjoint_step(const Plan &p, const Step &st, const void *in, void 
       });
     }
     case Step::AdjGather: {
-      const AdjPass &ps = p.adj.passes[st.index];
+      const AdjPass &ps = adjoint_pass(p, st.index, rb ? rb->tiled : batch * round_up(nt, kBlockTile));
       if (ps.block) {
         return for_each_launch(p, rb, st, true, ps.tile, batch, [&](auto r, unsigned gy, unsigned gz, const RaggedMap &rg) {
           AdjBlockLaunch g{dim3(static_cast<unsigned>(ps.nblocks), gy, gz), stream, rg, decltype(r)::value, ps.to_input, &ps,
@@ -1250,6 +1250,12 @@ const Pass &forward_pass(const Plan &p, int i, int64_t samples) {
   return whole ? many[i] : p.fwd.passes[i];
 }
 
+const AdjPass &adjoint_pass(const Plan &p, int i, int64_t samples) {
+  const std::vector<AdjPass> &many = p.adj.many;
+  const bool batch = i < static_cast<int>(many.size()) && many[i].samples > 0 && samples >= many[i].samples;
+  return batch ? many[i] : p.adj.passes[i];
+}
+
 int step_tile(const Plan &p, bool adjoint, int i, int64_t samples) {
   const Step &st = adjoint ? p.adj_steps[i] : p.fwd_steps[i];
   switch (st.kind) {
@@ -1259,7 +1265,7 @@ int step_tile(const Plan &p, bool adjoint, int i, int64_t samples) {
     case Step::MergeAdj:
     case Step::InitAdj: return kTile;
     case Step::AdjGather:
-      if (p.adj.passes[st.index].block) return p.adj.passes[st.index].tile;
+      if (p.adj.passes[st.index].block) return adjoint_pass(p, st.index, samples).tile;
       return adjoint_wave_span(p.gather_vecs, p.adj.passes[st.index].lagged) *
              (adjoint_threads(p, st.index) / 64 / adjoint_rows(p, st.index));
     case Step::Fused: {
@@ -1273,10 +1279,10 @@ int step_tile(const Plan &p, bool adjoint, int i, int64_t samples) {
   return 0;
 }
 
-int32_t step_extra(const Plan &p, bool adjoint, int i) {
+int32_t step_extra(const Plan &p, bool adjoint, int i, int64_t samples) {
   if (!adjoint) return 0;
   const Step &st = p.adj_steps[i];
-  return st.kind == Step::AdjGather && p.adj.passes[st.index].block ? p.adj.passes[st.index].extra : 0;
+  return st.kind == Step::AdjGather && p.adj.passes[st.index].block ? adjoint_pass(p, st.index, samples).extra : 0;
 }
 
 } // namespace fdmt

@@ -135,14 +135,15 @@ hipError_t launch_adjoint(const Plan &p, const void *grad_out, void *grad_in, in
 bool search_fusable(const Plan &p, int max_log2);
 hipError_t launch_forward_search(const Plan &p, const void *in, float *out, int batch, void *ws, BoxPartial *part,
                                  int max_log2, hipStream_t stream);
-// Forward pass i in the form that a batch of `samples` samples takes, each record
+// Forward (adjoint) pass i in the form that a batch of `samples` samples takes, each record
 // in whole tiles of kBlockTile.
 const Pass &forward_pass(const Plan &p, int i, int64_t samples);
+const AdjPass &adjoint_pass(const Plan &p, int i, int64_t samples);
 // Time-tile width of a step's launches for such a batch (0: one record); 0 when
 // the step has no ragged form.
 int step_tile(const Plan &p, bool adjoint, int step, int64_t samples = 0);
 // Samples past a record's end that a step's tiles cover (adjoint block passes).
-int32_t step_extra(const Plan &p, bool adjoint, int step);
+int32_t step_extra(const Plan &p, bool adjoint, int step, int64_t samples = 0);
 // Output rows per workgroup of adjoint register-gather pass `pass`.
 int adjoint_rows(const Plan &p, int pass);
 // Output rows and workgroup size of forward register-gather pass `ps`.

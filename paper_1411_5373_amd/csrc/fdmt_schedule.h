@@ -220,6 +220,8 @@ struct AdjPass {
   int k1 = 0, depth2 = 0, pitch = 0, tile = 0, nblocks = 0, rows_mid = 0;
   int32_t extra = 0;
   int64_t head_offset = 0, mid_offset = 0, out_offset = 0, leaf1_count = 0, leaf2_offset = 0;
+  bool few = false;     // smaller ranges than a batch of many records takes
+  int64_t samples = 0;  // samples of a batch from which it takes this form (see Pass::samples, AdjSchedule::many)
 };
 
 // Block passes of the adjoint. Between the planes l_hi and l_lo lies plane m =
@@ -264,6 +266,8 @@ struct AdjSchedule {
   std::vector<int32_t> starts;  // per pass: leaf index (pass-relative) of each row, then the end
   std::vector<int32_t> order;   // per pass: output row of each position (rows that share
                                 // leaves are neighbours, so they meet in one XCD's L2)
+  std::vector<AdjPass> many;         // block passes: their forms for batches of many[i].samples samples
+                                     // or more (0: the same form)
   std::vector<int32_t> block_heads;  // block passes: kAdjBlockHeader per block
   std::vector<int32_t> block_mids;   // ... first stage-1 leaf (pass-relative) of each LDS row, then the end
   std::vector<AdjBlockLeaf> block_leaves1;
