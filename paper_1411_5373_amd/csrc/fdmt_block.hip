@@ -220,8 +220,10 @@ __global__ __launch_bounds__(kBlockThreads, 8) void block_pass_kernel(const Tsrc
   int t0 = bs.tile * tiles * a.tile;
   for (int tile = 0; tile < tiles && t0 < nt; ++tile, t0 += a.tile) {
   if (K2 == 0 && tile > 0) __syncthreads();  // stage 3 of the tile before has read area A
-  if (t0 - room >= head[7] && t0 + kBlockPitch <= nt) {  // every sample of every term inside the record
-    row_batches<8 / N1>(wave, head[1], [&](int r, auto batch) {
+  // rows of which every sample of every term lies inside the record
+  const int fast = t0 - room >= head[7] && t0 + kBlockPitch <= nt ? head[8] : 0;
+  if (fast > 0) {
+    row_batches<8 / N1>(wave, fast, [&](int r, auto batch) {
       constexpr int RU = decltype(batch)::value;
       const Tsrc *p[RU][N1];  // wave-uniform
       int chain[RU][N1];
@@ -282,10 +284,12 @@ __global__ __launch_bounds__(kBlockThreads, 8) void block_pass_kernel(const Tsrc
         *reinterpret_cast<V *>(area_a + (r + u * kBlockWaves) * kBlockPitch + 4 * lane) = sum;
       }
     });
-  } else {
-    // record edges: each sample from its clamped place, zero before the record
-    // (past it the value does not matter: no sample before nt sums it)
-    for (int r = wave; r < head[1]; r += kBlockWaves) {
+  }
+  {
+    // record edges and rows with missing channels: each sample from its clamped
+    // place, zero before the record (past it the value does not matter: no sample
+    // before nt sums it)
+    for (int r = fast + wave; r < head[1]; r += kBlockWaves) {
       V v[N1];
 #pragma unroll
       for (int j = 0; j < N1; ++j) {
@@ -434,8 +438,9 @@ __global__ __launch_bounds__(kBlockThreads, 8) void packed_block_kernel(const ui
   int t0 = bs.tile * a.tiles_per_wg * a.tile;
   for (int tile = 0; tile < a.tiles_per_wg && t0 < nt; ++tile, t0 += a.tile) {
     if (K2 == 0 && tile > 0) __syncthreads();
-    if (t0 - room >= head[7] && t0 + kPitch <= nt) {
-      row_batches<8 / N1>(wave, head[1], [&](int r, auto batch) {
+    const int fast = t0 - room >= head[7] && t0 + kPitch <= nt ? head[8] : 0;
+    if (fast > 0) {
+      row_batches<8 / N1>(wave, fast, [&](int r, auto batch) {
         constexpr int RU = decltype(batch)::value;
         int mis[RU][N1], chain[RU][N1];
         Words2 x[RU][N1];
@@ -470,8 +475,9 @@ __global__ __launch_bounds__(kBlockThreads, 8) void packed_block_kernel(const ui
           put_row(r + u * kBlockWaves, even, odd);
         }
       });
-    } else {
-      for (int r = wave; r < head[1]; r += kBlockWaves) {
+    }
+    {
+      for (int r = fast + wave; r < head[1]; r += kBlockWaves) {
         uint32_t even[2] = {0, 0}, odd[2] = {0, 0};
         for (int j = 0; j < N1; ++j) {
           const Int4 e = terms[r * N1 + j];

@@ -721,8 +721,11 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
     const Node *na = level(0);
     const int count_a = 1 << kl;
     const int rows_a = bases(na, count_a, base_a);
-    int reach = 0;
+    int reach = 0, complete = 0;
     for (int j = 0; j < count_a; ++j) {
+      // positions without a channel are the last ones, so are the nodes that have them
+      const bool whole = !from_input || (na[j].sub + 1) << ps.k1 <= t.nf;
+      if (whole) complete = base_a[j] + na[j].nrows;
       for (int r = 0; r < na[j].nrows; ++r) {
         walk_terms(t, l0 + ps.k1, ps.k1, na[j].row0 + r, cur);
         for (int q = 0; q < terms1; ++q) {
@@ -735,7 +738,7 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
             // a position without a channel: past the start of every record, so zero
             const InTerm y = ch < t.nf ? InTerm{ch, shift + t.pre[ch], d, 0} : InTerm{0, kNoChannelPre, 0, 0};
             iterm[terms++] = y;
-            reach = std::max(reach, y.shift);
+            if (whole) reach = std::max(reach, y.shift);
             ps.staged_rows += d + 1;
             ps.max_chain = std::max(ps.max_chain, d);
           } else {
@@ -748,6 +751,7 @@ std::string build_block_pass(Schedule &s, const Tables &t, int64_t nt, int l0, i
     }
     head[1] = rows_a;
     head[7] = reach;
+    head[8] = complete;
     head[2] = static_cast<int32_t>(s.block_offs.size() - ps.offs_offset);
     const Node *below = na;
     std::vector<int> *base = &base_a;

@@ -119,8 +119,9 @@ constexpr int kBlockLead = 4;
 constexpr int kBlockTail = 4;
 // Per block: [0] first stage-1 term (pass-relative), [1] rows of A, [2] first
 // stage-2 offset, [3] rows of B, [4] first stage-3 offset, [5] output rows,
-// [6] first output row (plane l1), [7] largest shift of its stage-1 terms.
-constexpr int kBlockHeader = 8;
+// [6] first output row (plane l1), [8] rows of A without a missing channel (they come
+// first), [7] the largest shift of their terms.
+constexpr int kBlockHeader = 16;
 constexpr int kBlockTile = 224;    // time tile where the shifts of a block spread as little as they mostly do
 constexpr int kBlockLevels = 6;    // most iterations of a block pass
 constexpr int kBlockMaxChain = kBlockLead;  // longest Option-1 chain a first pass from the input adds up itself
