@@ -177,7 +177,7 @@ __device__ __forceinline__ void box_stats(const Float4 (&v)[C], int nvalid, int 
     if (FULL) {
       top[c] = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(v[c][0], v[c][1]), v[c][2]), v[c][3]);
     } else {
-      top[c] = -__builtin_inff();
+      top[c] = __builtin_nanf("");  // stays one, equal to no peak, without a valid sample that is a number
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (256 * c + 4 * lane + i < nvalid) top[c] = __builtin_fmaxf(top[c], v[c][i]);
@@ -194,13 +194,7 @@ __device__ __forceinline__ void box_stats(const Float4 (&v)[C], int nvalid, int 
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     if (at != INT32_MAX) continue;
-    bool here = top[c] == peak;
-    if (!FULL) {
-      // a lane without a valid sample, or with NaNs alone, has the -inf its top started at
-      here = false;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) here = here || (256 * c + 4 * lane + i < nvalid && v[c][i] == peak);
-    }
+    const bool here = top[c] == peak;
     const uint64_t lanes = __builtin_amdgcn_ballot_w64(here);
     if (lanes) {
       int i = 3;
@@ -248,10 +242,7 @@ __device__ __forceinline__ void box_warm(Float4 (&v)[C], BoxHistory &h, float *b
 }
 
 // A row's last tile of nvalid samples, at most C chunks (nothing follows that
-// would need its history). Rows of kBoxFew chunks or fewer had the work of a
-// whole tile: 50000 rows of 50 samples with widths 1..32 took 163 us with every
-// width in LDS, 221 us with tiles in registers and now 127 us.
-constexpr int kBoxFew = 2;  // the widest history, 512 samples, takes as many
+// would need its history).
 template <int M, int C>
 __device__ __forceinline__ void box_last_tile(const float *y, BoxHistory &h, float *buf, int lane, int nvalid,
                                               BoxSums<M> &sums, BoxPartial *p, int64_t width_stride, int32_t t0) {
@@ -266,8 +257,14 @@ __device__ __forceinline__ void box_last_tile(const float *y, BoxHistory &h, flo
   box_widths<M, 0, false>(v, h, buf, lane, nvalid, sums, p, width_stride, t0);
 }
 
+// Rows of kBoxFew chunks or fewer (SHORT) do no more than those chunks: 50000
+// rows of 50 samples with widths 1..32 took 163 us with every width in LDS, 221
+// us as whole tiles and now 113 us. Other rows' last tiles are whole ones: with a
+// form for few chunks beside, the search of long rows was 3% slower.
+constexpr int kBoxFew = 2;  // the widest history, 512 samples, takes as many
+
 // Three waves per SIMD: at four (128 VGPRs) the widest searches spill, 0.36 ms.
-template <int M>
+template <int M, bool SHORT>
 __global__ __launch_bounds__(kBoxThreads, 3) void boxcar_tile_kernel(const float *__restrict__ plane,
                                                                   BoxPartial *__restrict__ part, int64_t nt,
                                                                   int32_t nd, int32_t ntiles, int32_t span) {
@@ -295,17 +292,17 @@ __global__ __launch_bounds__(kBoxThreads, 3) void boxcar_tile_kernel(const float
   for (int tile = first; tile < last; ++tile) {
     const int64_t t0 = static_cast<int64_t>(tile) * kBoxTile;
     const int64_t left = nt - t0;
-    Float4 v[kBoxChunks];
-    if (left >= kBoxTile) {
+    if (SHORT) {
+      box_last_tile<M, kBoxFew>(y + t0, h, buf, lane, static_cast<int>(left), sums, p + tile, width_stride,
+                                static_cast<int32_t>(t0));
+    } else if (left >= kBoxTile) {
+      Float4 v[kBoxChunks];
 #pragma unroll
       for (int c = 0; c < kBoxChunks; ++c) v[c] = *reinterpret_cast<const Float4u *>(y + t0 + 256 * c + 4 * lane);
       box_widths<M, 0, true>(v, h, buf, lane, kBoxTile, sums, p + tile, width_stride, static_cast<int32_t>(t0));
-    } else if (left > 256 * kBoxFew) {
+    } else {
       box_last_tile<M, kBoxChunks>(y + t0, h, buf, lane, static_cast<int>(left), sums, p + tile, width_stride,
                                    static_cast<int32_t>(t0));
-    } else {
-      box_last_tile<M, kBoxFew>(y + t0, h, buf, lane, static_cast<int>(left), sums, p + tile, width_stride,
-                                static_cast<int32_t>(t0));
     }
   }
   // the span's sums go to its first tile's partials
@@ -526,8 +523,12 @@ hipError_t launch_boxcar_tiles(const float *plane, int32_t batch, int32_t nd, in
   const dim3 grid(static_cast<unsigned>((ntiles + span - 1) / span), nd, batch);
 #define FDMT_BOX(MM)                                                                                             \
   case MM:                                                                                                       \
-    hipLaunchKernelGGL(boxcar_tile_kernel<MM>, grid, dim3(kBoxThreads), 0, stream, plane, part, nt, nd,           \
-                       static_cast<int32_t>(ntiles), span);                                                      \
+    if (nt <= 256 * kBoxFew)                                                                                     \
+      hipLaunchKernelGGL((boxcar_tile_kernel<MM, true>), grid, dim3(kBoxThreads), 0, stream, plane, part, nt, nd, \
+                         static_cast<int32_t>(ntiles), span);                                                    \
+    else                                                                                                         \
+      hipLaunchKernelGGL((boxcar_tile_kernel<MM, false>), grid, dim3(kBoxThreads), 0, stream, plane, part, nt,    \
+                         nd, static_cast<int32_t>(ntiles), span);                                                \
     break;
   switch (max_log2) {
     FDMT_BOX(0) FDMT_BOX(1) FDMT_BOX(2) FDMT_BOX(3) FDMT_BOX(4) FDMT_BOX(5)
