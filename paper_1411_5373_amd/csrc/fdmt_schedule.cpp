@@ -1018,15 +1018,19 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
     ps.pitch = workgroups(512) >= 1024 ? 512 : 256;
     const int align = ps.pitch == 512 ? 32 : 4;
     // Fewer rows of plane m per range where the blocks would leave CUs idle: ranges
-    // are halved until there are as many workgroups as run at once (Nf=64, Nt=20000,
-    // Nd=64 15.8 us, 22 us with 256 of them; Nf=1024, Nt=Nd=1000 24.6 and 32.6 us). A
-    // batch has them anyway, and larger ranges make fewer rows twice. A sub-band of no more than `most` rows stays whole,
-    // no row of it made twice, unless half the GPU would be idle.
+    // are halved while there are less than 768 workgroups of the 1024 that run at
+    // once (Nf=64, Nt=20000, Nd=64 15.8 us, 22 us with 256 of them; Nf=1024, Nt=Nd=1000
+    // 24.6 and 32.6 us; at 1024 other shapes lost up to 10%). A batch has them anyway,
+    // and larger ranges make fewer rows twice; so do few rows in one or two blocks,
+    // which are halved below 256 only (Nf=100, Nt=100000, Nd=16 28 us, 28.7 us). A
+    // sub-band of no more than `most` rows stays whole, no row of it made twice,
+    // unless half the GPU would be idle.
     int most = kAdjBlockRows;
-    while (own > 7 && ps.pitch == 256 && workgroups(ps.pitch) < (many ? 256 : 1024)) {
+    const int enough = many || rows <= 2 * own ? 256 : 768;
+    while (own > 7 && ps.pitch == 256 && workgroups(ps.pitch) < enough) {
       ps.few = ps.few || workgroups(ps.pitch) >= 256;
       own /= 2;
-      if (many || workgroups(ps.pitch) < 600) most = own;
+      if (enough == 256 || workgroups(ps.pitch) < 600) most = own;
     }
     // Ranges, gathered into blocks while their rows fit LDS and their outputs'
     // offsets lie together: a block runs the windows between its smallest and its
@@ -1143,14 +1147,16 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
     ps.leaves = ps.leaf1_count;
     ps.tile = (ps.pitch - spread) / align * align;
     if (ps.tile < 128 || spread > 128) return "block shifts spread too far";
-    // T0 = 0 is the same time in every block where the record is much longer than
-    // the offsets: blocks then read plane l_hi over one time. A smallest delay, or a
-    // short record, would make many of them windows that no output of the block
-    // lies in: there T0 = 0 is each block's own first window
-    // (Nf=1024, Nt=1024, Nd=64, smallest delay 100000: 32481 workgroups of the last
-    // pass, now 1568, and the adjoint 72 us, now 17 us; register gathers 19 us).
+    // T0 = 0 is the same time in every block where the record is longer than the
+    // offsets: blocks then read plane l_hi over one time (three beams of Nf=1024,
+    // Nt=3283, Nd=1823, offsets half a record, 55 us for the first pass, 61 us each
+    // from its own). A smallest delay, or a shorter record, would make most of them
+    // windows that no output of the block lies in: there T0 = 0 is each block's own
+    // first window (Nf=1024, Nt=1024, Nd=64, smallest delay 100000: 32481 workgroups
+    // of the last pass, now 1568, and the adjoint 72 us, now 17 us; register gathers
+    // 19 us).
     for (const Block &b : blocks) ps.extra = std::max(ps.extra, b.head[5]);
-    const bool own_start = to_input || 4 * static_cast<int64_t>(ps.extra) > nt;
+    const bool own_start = to_input || ps.extra > nt;
     ps.extra = 0;
     for (Block &b : blocks) {
       if (const int32_t first = own_start ? b.head[6] / ps.tile * ps.tile : 0) {
