@@ -1122,7 +1122,18 @@ std::string build_adjoint_block_pass(AdjSchedule &s, const Tables &t, int64_t nt
     for (int x = 0; x < subs; ++x) {
       const int n = t.rows[m][x];
       const int32_t off = static_cast<int32_t>(t.row_off[m][x]);
-      const int parts = n <= most ? 1 : row_parts(n, own, subs);
+      // A range's stage 1 has a leaf for each row of plane l_hi that it reads: under
+      // a wide sub-band of plane l_hi 28 rows read up to 300, against 60 and 150 in
+      // the blocks beside them, and a few such blocks were the tail of a pass
+      // (Nf=Nd=1024, Nt=16384, 0.4-0.8 GHz, one record: first pass 72 us in 38 blocks,
+      // 67 us in 40 that are no lighter, 43 us in these 40; the adjoint 144 and 120 us,
+      // of 16 records 1845 and 1780 us). Bounds of 185 to 245 leaves measure alike,
+      // 160 and less make too many rows twice (1.1-1.9 GHz 5% slower), 270 changes
+      // nothing. Where heavy blocks were no tail, the rows made twice cost up to 4%
+      // (Nt=8192, 0.3-0.9 GHz).
+      const int64_t leaves1 = t.rows[l_hi][x >> shape.k1];
+      const int each = static_cast<int>(std::clamp<int64_t>(int64_t(n) * 240 / leaves1, std::min(own, 7), own));
+      const int parts = n <= most ? 1 : row_parts(n, each, subs);
       size_t i = out_of[x];
       for (int b = 0; b < parts; ++b) {
         const int32_t end = off + static_cast<int32_t>(static_cast<int64_t>(n) * (b + 1) / parts);
