@@ -107,8 +107,8 @@ typedef enum {
  * gather_vecs zero the adjoint does, up to four. A nonzero field selects the other
  * forms for its direction, whose own defaults the comments below give; they also
  * run shapes that block passes do not cover (fewer than three iterations, or two
- * for the adjoint; shifts within a block that spread past its window; an Nt of
- * more than 65535 tiles). */
+ * for the adjoint; shifts within a block that spread past its window; for the
+ * adjoint a d_min of many records; an Nt of more than 65535 tiles). */
 typedef struct {
   int32_t in_dtype;       /* fdmt_dtype_t of the forward input */
   int32_t acc_dtype;      /* FDMT_F32 or FDMT_I32 */

@@ -17,8 +17,8 @@
 //
 // Measured (one MI355X, register gathers -> block passes): Nf=4096, Nt=65536,
 // Nd=2048 1.33 -> 1.05 ms (3.7 TB/s of plane traffic); batch 16 of Nf=1024,
-// Nt=16384, Nd=1024 2.51 -> 1.84 ms; Nf=2048, Nt=30003, Nd=1500 0.59 -> 0.35 ms;
-// Nf=1000, Nt=40001, Nd=900 0.41 -> 0.29 ms. Bound by latency and issue: with
+// Nt=16384, Nd=1024 2.51 -> 1.79 ms; Nf=2048, Nt=30003, Nd=1500 0.59 -> 0.35 ms;
+// Nf=1000, Nt=40001, Nd=900 0.41 -> 0.28 ms. Bound by latency and issue: with
 // neither loads nor stores the passes take 0.55 of their time.
 #include <hip/hip_runtime.h>
 

@@ -340,13 +340,14 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
     // the d_min pre-shift rides on the input terms of a gather from the input
     else if (o.d_min > 0) sp.first_kind = fdmt::PassKind::Register;
     if (o.later_kernel) sp.later_kind = kinds[o.later_kernel];
-    // Block passes (fdmt_block.hip) are the default: at every shape measured
+    // Block passes (fdmt_block.hip) are the default: at every shape measured but one
     // they beat the other forms, also the tuned register gathers, from Nf=64,
-    // Nt=1024 (8 us against 23 us) to Nf=4096, Nt=65536 (0.56 ms against 0.78 ms,
-    // uint8). A nonzero forward schedule field asks for another form, and these
-    // also run what block passes do not cover: fewer than three iterations,
-    // block shifts that spread past half a tile, or an Nt with more block tiles
-    // than the grid's y dimension holds.
+    // Nt=1024 (7.3 us against 23 us) to Nf=4096, Nt=65536 (0.54 ms against 0.78 ms,
+    // uint8); 16 beams of Nf=1024, Nt=1024 whose smallest delay is ten records long
+    // take 35.5 us, 34.3 us with the LDS first pass. A nonzero forward schedule field
+    // asks for another form, and these also run what block passes do not cover:
+    // fewer than three iterations, block shifts that spread past half a tile, or an
+    // Nt with more block tiles than the grid's y dimension holds.
     const bool open = !o.first_levels && !o.later_levels && !o.tile && !o.lds_kib && !o.max_block_rows &&
                       !o.first_kernel && !o.later_kernel && !o.stream_tiles && !o.gather_rows && !o.gather_threads &&
                       !o.first_rows && !o.first_threads;
@@ -371,10 +372,13 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
       const int per = o.adjoint_levels ? o.adjoint_levels : 2;
       const int last = o.adjoint_last_levels ? o.adjoint_last_levels : 2;
       // Block passes (fdmt_adjoint_block.hip) unless an adjoint or gather field
-      // asks for the register gathers: faster from Nf=64, Nt=1024 (11.5 us against
-      // 16.8 us) to Nf=4096, Nt=65536 (1.05 ms against 1.33 ms tuned). The register
-      // gathers also run what block passes do not cover: fewer than two iterations,
-      // shifts that spread past 128 samples in a block, an Nt with too many tiles.
+      // asks for the register gathers: faster from Nf=64, Nt=1024 (9.3 us against
+      // 12.5 us) to Nf=4096, Nt=65536 (1.05 ms against 1.33 ms tuned) at all but two of
+      // 180 shapes, where they are up to 4% slower (Nf=32, Nt=100000, Nd=64 44 us
+      // against 42 us). The register gathers also run what block passes do not cover:
+      // fewer than two iterations, shifts that spread past 128 samples in a block,
+      // offsets of a block that spread past twice the record (a smallest delay of
+      // many records), an Nt with too many tiles.
       const bool open = !o.adjoint_levels && !o.adjoint_last_levels && !o.adjoint_last_rows && !o.adjoint_rows &&
                         !o.adjoint_tile_major && !o.adjoint_threads && !o.adjoint_last_threads && !o.gather_rows &&
                         !o.gather_vecs;

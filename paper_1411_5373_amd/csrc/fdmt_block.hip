@@ -17,10 +17,10 @@
 // are no faster, and four or eight tiles slower).
 //
 // Measured (one MI355X, register gathers -> block passes): Nf=4096, Nt=65536,
-// Nd=2048 uint8 0.776 -> 0.562 ms, FP32 1.238 -> 0.858 ms; batch 16 of
-// Nf=1024, Nt=16384, Nd=1024 FP32 2.120 -> 1.229 ms (3.5 TB/s of plane
-// traffic); Nf=1000, Nt=40001, Nd=900 uint8 0.240 -> 0.098 ms; Nf=64, Nt=1024,
-// Nd=64 FP32 0.023 -> 0.008 ms (one launch). What bounds a pass now is its
+// Nd=2048 uint8 0.776 -> 0.53-0.57 ms, FP32 1.238 -> 0.85-0.90 ms; batch 16 of
+// Nf=1024, Nt=16384, Nd=1024 FP32 2.120 -> 1.23 ms (3.5 TB/s of plane
+// traffic); Nf=1000, Nt=40001, Nd=900 uint8 0.240 -> 0.096 ms; Nf=64, Nt=1024,
+// Nd=64 FP32 0.023 -> 0.007 ms (one launch). What bounds a pass now is its
 // instruction stream and the latency between its stages: without loads and
 // stores a six-iteration pass of the first workload still takes 0.18 ms, its
 // loads and stores add 0.1 ms each.
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kBlockThreads, 8) void block_pass_kernel(const Tsrc
         V sum;
         if constexpr (FROM_INPUT && std::is_same<Tsrc, uint8_t>::value && std::is_same<Tacc, int32_t>::value) {
           // integer sums of bytes in any order: two 16-bit sums per word
-          // (at most 2^3 chains of 5 bytes), samples 0 and 2, and 1 and 3
+          // (at most 2^K1 = 4 chains of 5 bytes), samples 0 and 2, and 1 and 3
           uint32_t even = 0, odd = 0;
 #pragma unroll
           for (int j = 0; j < N1; ++j) {

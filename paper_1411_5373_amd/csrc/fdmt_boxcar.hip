@@ -52,7 +52,7 @@ __device__ __forceinline__ T xor_lane(T x, int mask) {
 // the FP64 sums are reduced across the wave once per span (a tile's own are
 // never used). With every width in LDS, a peak test per sample and a reduction
 // per tile and width, widths 1..256 over 2048 x 65536 took 0.62 ms; this takes
-// 0.33 ms at 76% of the vector ALU's issue rate (reading the plane takes 0.1 ms).
+// 0.30-0.33 ms at 76% of the vector ALU's issue rate (reading the plane takes 0.1 ms).
 constexpr int kBoxChunks = kBoxTile / 256;
 
 typedef float Float4 __attribute__((ext_vector_type(4)));
