@@ -373,8 +373,8 @@ fdmt_status_t fdmt_plan(fdmt_plan_t *out, int32_t nf, int64_t nt, int32_t nd, do
       const int last = o.adjoint_last_levels ? o.adjoint_last_levels : 2;
       // Block passes (fdmt_adjoint_block.hip) unless an adjoint or gather field
       // asks for the register gathers: faster from Nf=64, Nt=1024 (9.3 us against
-      // 12.5 us) to Nf=4096, Nt=65536 (1.05 ms against 1.33 ms tuned) at all but two of
-      // 180 shapes, where they are up to 4% slower (Nf=32, Nt=100000, Nd=64 44 us
+      // 12.5 us) to Nf=4096, Nt=65536 (1.05 ms against 1.33 ms tuned) at all but three of
+      // 200 shapes, where they are up to 4% slower (Nf=32, Nt=100000, Nd=64 44 us
       // against 42 us). The register gathers also run what block passes do not cover:
       // fewer than two iterations, shifts that spread past 128 samples in a block,
       // offsets of a block that spread past twice the record (a smallest delay of
